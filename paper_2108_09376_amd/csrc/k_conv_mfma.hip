@@ -96,6 +96,7 @@ struct MfmaArgs {
     int x_bytes, w_bytes, y_bytes;      // buffer extents
     FastDiv f_hrhc, f_hc, f_rbw, f_bw;  // divisions by HR*HC, HC, R*bw, bw
     int ksplit, cps;                    // K slices per tile, 32-channel chunks per slice
+    int kseq;                           // wave-K form: slices one workgroup runs in order
     int tiles_full;                     // tiles (incl. K slices) of a full frame
     int slots;                          // stem form: workgroups resident on the device
     int xu, gx;                         // XCD grouping of the tile order (xcd_tile), 0 = off
@@ -860,6 +861,252 @@ __global__ __launch_bounds__(kThreads) void k_conv_pipe_pair(MfmaArgs a1, MfmaAr
         conv_pipe_tile<BF16, 64, BN2, 1, 1, SG2>(a2, (int)blockIdx.x - grid1);
 }
 
+// ------------------------------------------------------------------ wave-K form (3x3, stride 1)
+//
+// Layers with a long K on few tiles ran one workgroup per CU, one wave per SIMD, through
+// stages in which nothing overlaps: registers stored to LDS, barrier, loads requested,
+// fragments read, products. Here the four waves of a 64x64 tile split K instead of the
+// tile: wave w takes the 32-channel chunks w, w + 4, ... of the slice with all their
+// taps and accumulates the whole tile (4 x 4 fragments, so a product needs half the LDS
+// bytes that 32x32 per wave need). A wave shares nothing with the others until the end:
+//  * its halo chunk (double buffer) and its weight slices (a ring of D taps) go straight
+//    from memory into its own part of LDS (buffer loads with an LDS destination), without
+//    registers, stores or barriers; out-of-range lanes write zeros;
+//  * it waits only for its own requests (vmcnt counts, known at compile time for every
+//    tap), and reads the next tap's fragments while the current tap's products run;
+//  * a row (pixel slot or output channel) is 64 bytes, its 16-byte quarter q stored at
+//    q ^ ((row >> 1) & 3): the loads write 1 KB linearly, so the swizzle is in which
+//    quarter a lane requests, and eight consecutive rows read at one quarter use all banks.
+// The four partial tiles are added through LDS in wave order, wave w finishing quadrant w.
+// The order of the sums depends on the layer's shape only.
+
+// Raw buffer descriptor as the four dwords that the inline instruction takes.
+__device__ __forceinline__ i32x4 raw_desc(const void *p, int bytes)
+{
+    const uint64_t u = (uint64_t)p;
+    return i32x4{(int)(uint32_t)u, (int)(uint32_t)(u >> 32), bytes, kBufferFlags};
+}
+
+// 64 lanes x 16 bytes from memory to LDS bytes [lds, lds + 1024) (lane i at 16 i). No
+// register receives data; offsets at or beyond the buffer's extent write zeros.
+__device__ __forceinline__ void dma16(const i32x4 &r, uint32_t lds, int voff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(r) : "memory");
+}
+
+// At most N requests of this wave outstanding, and every LDS read done (the slot the
+// last fragments came from may be overwritten).
+template <int N>
+__device__ __forceinline__ void wait_dma()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory");
+}
+
+__device__ __forceinline__ uint32_t lds_addr(const void *p)
+{
+    return (uint32_t)(uint64_t)(__attribute__((address_space(3))) const uint8_t *)p;
+}
+
+// Adds the four waves' partial tiles (4 x 4 fragments) in wave order; wave w gets quadrant
+// (w >> 1, w & 1) as 2 x 2 fragments. Needs 64 KB of LDS at smem that no wave uses
+// any more after the first barrier.
+__device__ __forceinline__ void join_waves(f32x4 (&acc)[4][4], f32x4 (&out)[2][2], uint8_t *smem,
+                                           int wave, int lane)
+{
+    f32x4 *part = (f32x4 *)smem + lane;
+    __syncthreads();
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) {
+        if (wave == qd) {
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+                out[f >> 1][f & 1] = acc[(qd >> 1) * 2 + (f >> 1)][(qd & 1) * 2 + (f & 1)];
+        } else {
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+                part[((qd * 4 + wave) * 4 + f) * 64] = acc[(qd >> 1) * 2 + (f >> 1)][(qd & 1) * 2 + (f & 1)];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        f32x4 v[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            v[w] = out[f >> 1][f & 1];
+            if (w != wave) v[w] = part[((wave * 4 + w) * 4 + f) * 64];
+        }
+        out[f >> 1][f & 1] = ((v[0] + v[1]) + v[2]) + v[3];
+    }
+}
+
+// LDS bytes of one wave: two halo chunks of HA KB and D weight slices of 4 KB, D as many
+// as 160 KB for four waves allow (5 taps of 64x64 products, about 0.9 us, cover a miss).
+constexpr int wavek3_bytes(int HA, int D) { return 2 * HA * 1024 + D * 4096; }
+constexpr int wavek3_depth(int HA) { return HA <= 7 ? 6 : HA <= 9 ? 5 : 3; }
+
+template <bool BF16, int HA>
+__global__ __launch_bounds__(kThreads, 1) void k_conv_wavek3(MfmaArgs a)
+{
+    constexpr int KT = 9, HB = HA * 1024, D = wavek3_depth(HA);
+    static_assert(D >= 3 && D <= 9 && 4 * (D - 1) + HA <= 63, "outstanding requests fit vmcnt");
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ TileBlocks tb;
+    __shared__ int s_last;
+    const int L = blockIdx.x;
+    const int ks = L % a.ksplit, mn = L / a.ksplit;
+    const int nt = mn % a.ntn, mt = mn / a.ntn;
+    const int n0 = nt * 64;
+    if (!load_tile_blocks(a, mt, tb)) return;   // tile beyond the active count (uniform)
+    Epilogue<BF16, 64, 64> epi;
+    epi.prefetch(a, tb, n0);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = (lane & 3) ^ ((lane >> 3) & 3);        // quarter this lane requests
+    const int nchunk = (a.cin + BK - 1) / BK;
+    const i32x4 xd = raw_desc(a.x, a.x_bytes), wd = raw_desc(a.w, a.w_bytes);
+    uint8_t *base = smem + wave * wavek3_bytes(HA, D);
+    uint8_t *ring = base + 2 * HB;
+    const uint32_t lbase = __builtin_amdgcn_readfirstlane(lds_addr(base));
+    const uint32_t lring = lbase + 2 * HB;
+    const int hrhc = a.HR * a.HC;
+
+    int aoff[HA];
+#pragma unroll
+    for (int u = 0; u < HA; ++u) {
+        const int slot = 16 * u + (lane >> 2);
+        const int p = min(fdiv(slot, a.f_hrhc), a.P - 1);
+        const int r = slot - p * hrhc;
+        const int hy = fdiv(r, a.f_hc), hx = r - hy * a.HC;
+        const int img = tb.img[p];
+        const int iy = tb.oy0[p] - a.pad + hy, ix = tb.ox0[p] - a.pad + hx;
+        const bool in = slot < a.nslot && img >= 0 && iy >= 0 && iy < a.hin && ix >= 0 && ix < a.win;
+        const int off = (((img * a.hin + iy) * a.win + ix) * a.cin + q * 8) * 2;
+        aoff[u] = in ? off : kOutOfRange;
+    }
+    auto issue_a = [&](int c, int buf) {
+        const bool ok = c * BK + q * 8 < a.cin;
+#pragma unroll
+        for (int u = 0; u < HA; ++u)
+            dma16(xd, lbase + buf * HB + u * 1024, ok && aoff[u] != kOutOfRange ? aoff[u] + c * BK * 2 : kOutOfRange);
+    };
+    const int woff = ((n0 + (lane >> 2)) * KT * a.cin + q * 8) * 2;
+    const int wstep = 16 * KT * a.cin * 2;               // bytes between 16 output channels
+    // 16 output channels (v) of one tap's slice
+    auto issue_w = [&](int c, int tap, int slot, int v) {
+        const int off = woff + (tap * a.cin + c * BK) * 2 + v * wstep;
+        dma16(wd, lring + slot * 4096 + v * 1024, c * BK + q * 8 < a.cin ? off : kOutOfRange);
+    };
+    int sl[4];                                           // halo slot of this lane's rows at tap (0, 0)
+    const int rbw = a.R * a.bw;
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi) {
+        const int m = mi * 16 + (lane & 15);
+        const int p = fdiv(m, a.f_rbw);
+        const int local = m - p * rbw;
+        const int pr = fdiv(local, a.f_bw), pc = local - pr * a.bw;
+        sl[mi] = p * hrhc + pr * a.HC + pc;
+    }
+    const int bo = (lane & 15) * 64 + (((lane >> 4) ^ ((lane >> 1) & 3)) << 4);
+    auto read_a = [&](int tap, int buf, int mi) {
+        const int s = sl[mi] + (tap / 3) * a.HC + tap % 3;
+        return *(const short8 *)(base + buf * HB + s * 64 + (((lane >> 4) ^ ((s >> 1) & 3)) << 4));
+    };
+    auto read_b = [&](int slot, int ni) { return *(const short8 *)(ring + slot * 4096 + ni * 1024 + bo); };
+    // one K slice: the four waves' chunks [s_lo, s_hi), joined into out
+    auto slice = [&](int s_lo, int s_hi, f32x4 (&out)[2][2]) {
+        f32x4 acc[4][4];
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < 4; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int c0 = s_lo + wave;
+        const int nc = c0 < s_hi ? (s_hi - c0 + 3) / 4 : 0;  // this wave's chunks
+        if (nc > 0) {
+            short8 af[4], bf[4];
+            int slot = 0;                                    // ring slot of the current tap
+            issue_a(c0, 0);
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) issue_w(c0, d, d, v);
+            wait_dma<4 * (D - 1)>();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                af[i] = read_a(0, 0, i);
+                bf[i] = read_b(0, i);
+            }
+            auto chunk = [&](auto last_c, int j) {
+                constexpr bool LAST = decltype(last_c)::value;
+                const int c = c0 + 4 * j, buf = j & 1;
+                auto step = [&](auto tap_c) {
+                    constexpr int tap = decltype(tap_c)::value;
+                    // requests younger than the next tap's weights: D - 2 taps (fewer at the
+                    // end), and the next halo chunk while those weights were requested before it
+                    constexpr int WN = LAST ? (7 - tap < D - 2 ? 7 - tap : D - 2) : D - 2;
+                    constexpr int HN = !LAST && tap >= 1 && tap <= D - 2 ? HA : 0;
+                    constexpr bool MORE = !(LAST && tap == 8);
+                    const int next = slot + 1 == D ? 0 : slot + 1;
+                    short8 an[4], bn[4];
+                    if constexpr (MORE) wait_dma<4 * WN + HN>();
+                    if constexpr (!LAST && tap == 0) issue_a(c + 4, buf ^ 1);
+                    // two products, one fragment read and (in the first half) one request at a
+                    // time, so that none of the three waits for the others to be issued
+#pragma unroll
+                    for (int g = 0; g < 8; ++g) {
+                        const int mi = g >> 1, n2 = (g & 1) * 2;
+                        if constexpr (MORE) {
+                            if (g < 4) bn[g] = read_b(next, g);
+                            else an[g - 4] = tap < 8 ? read_a(tap + 1, buf, g - 4) : read_a(0, buf ^ 1, g - 4);
+                        }
+                        acc[mi][n2] = mfma<BF16>(af[mi], bf[n2], acc[mi][n2]);
+                        acc[mi][n2 + 1] = mfma<BF16>(af[mi], bf[n2 + 1], acc[mi][n2 + 1]);
+                        if (g & 1) {
+                            if constexpr (tap + D < KT) issue_w(c, tap + D, slot, mi);
+                            else if constexpr (!LAST) issue_w(c + 4, tap + D - KT, slot, mi);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (MORE) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            af[i] = an[i];
+                            bf[i] = bn[i];
+                        }
+                    }
+                    slot = next;
+                };
+                step(std::integral_constant<int, 0>{});
+                step(std::integral_constant<int, 1>{});
+                step(std::integral_constant<int, 2>{});
+                step(std::integral_constant<int, 3>{});
+                step(std::integral_constant<int, 4>{});
+                step(std::integral_constant<int, 5>{});
+                step(std::integral_constant<int, 6>{});
+                step(std::integral_constant<int, 7>{});
+                step(std::integral_constant<int, 8>{});
+            };
+            for (int j = 0; j + 1 < nc; ++j) chunk(std::false_type{}, j);
+            chunk(std::true_type{}, nc - 1);
+        }
+        join_waves(acc, out, smem, wave, lane);
+    };
+    f32x4 sum[2][2];
+    slice(ks * a.cps, min(nchunk, ks * a.cps + a.cps), sum);
+    for (int i = 1; i < a.kseq; ++i) {                   // this workgroup's further slices, in order
+        f32x4 part[2][2];
+        __syncthreads();                                 // the join's partial sums are read
+        slice(i * a.cps, min(nchunk, i * a.cps + a.cps), part);
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) sum[mi][ni] = sum[mi][ni] + part[mi][ni];
+    }
+    if (a.ksplit > 1 && !split_k_handoff(a, sum, mt * a.ntn + nt, ks, &s_last)) return;
+    epi.finish(a, sum, smem, n0);
+}
+
 // ------------------------------------------------------------------ stem form
 //
 // Layers with few input channels (the RGB stem): Cin <= 4 with kw <= 8, or Cin <= 8 with
@@ -1122,6 +1369,7 @@ struct Plan {
     MfmaArgs a;
     int sg = 1;                // pipelined form: stage grouping (k_conv_pipe's SG)
     int wgs = 1;               // pipelined form: groups of four waves per tile (K halves)
+    int wavek = 0;             // wave-K form: KB of one halo chunk (0: another form)
     unsigned tiles;            // output tiles of a full frame (before any K split)
     size_t lds;
     size_t ws_bytes;
@@ -1182,10 +1430,12 @@ bool make_plan(const LayerGeom &g, int BM, int BN, Plan &pl)
     a.xu = a.gx = 0;
     a.grp_lds = 0;
     pl.wgs = 1;
+    pl.wavek = 0;
     if (g.cout % BN) return false;
     if (!tile_rows(g, BM, a)) return false;
     const int KS = g.kh, S = g.stride;
     a.ksplit = 1;
+    a.kseq = 1;
     a.cps = (g.cin + BK - 1) / BK;
     pl.ws_bytes = 0;
     if (g.cin % 8) {
@@ -1294,6 +1544,35 @@ bool choose_plan(const LayerGeom &g, Plan &best)
                     best.sg = 9;
                     best.lds = lds;
                 }
+            }
+            // Wave-K form (k_conv_wavek3): stride-1 3x3 layers with a chunk per wave and at
+            // most 512 tiles, or 16 chunks and at most 2048 (measured, us per launch, before
+            // -> with it, at 38 of 128 blocks / every block: 256->256 at stride 16 12.5 -> 9.6
+            // / 24.2 -> 18.2; 512->512 at stride 32 14.9 -> 12.0 / 28.2 -> 16.4, at stride 16
+            // 30.4 -> 24.9 / 70.4 -> 53.3; 128->128 on 256 tiles 8.3 -> 7.5 / 9.2 -> 8.0). Not
+            // with two chunks (64->256 on 128 tiles: 6.5 -> 7.1, two waves have no work) and
+            // not for many short tiles (128->128 on 1024 tiles 11.9 -> 14.6, 256->256 on 2048
+            // 26.4 -> 27.3): one 150 KB workgroup per CU overlaps no tile's start and end.
+            // More than 256 tiles keep K whole: two slices as workgroups of their own cost
+            // 512->512 at stride 16 25 -> 32 us. A call without an index runs every tile: if
+            // its slices are more workgroups than CUs, each tile's workgroup runs them in
+            // turn (same sums, same order; 512->512 at stride 32, every block, 22.4 -> 16.4).
+            if (g.kh == 3 && g.stride == 1 && best.BM == 64 && best.BN == 64 && a.nslot <= 192 &&
+                ((nchunk >= 4 && tiles <= 512) || (nchunk >= 16 && tiles <= 2048))) {
+                // ws_bytes stays: which layers need the workspace, and are refused without it,
+                // is documented by shape and does not change with the form
+                if (tiles > 256) {
+                    a.ksplit = 1;
+                    a.cps = nchunk;
+                    best.grid = tiles;
+                }
+                if (!g.count && best.grid > 256) {
+                    a.kseq = a.ksplit;
+                    a.ksplit = 1;
+                    best.grid = tiles;
+                }
+                best.wavek = a.nslot <= 112 ? 7 : a.nslot <= 144 ? 9 : 12;
+                best.lds = 4 * (size_t)wavek3_bytes(best.wavek, wavek3_depth(best.wavek));
             }
             // 1x1 layers with 64x64 tiles stage two chunks per barrier (a same-process A/B
             // of full ResNet-50 frames: 0.6642 -> 0.6583 ms; with 64x128 tiles, or four
@@ -1459,6 +1738,11 @@ hipError_t launch_one(const Plan &p, hipStream_t s)
         }
     } else if (p.form == Form::Pipe) {
         if constexpr (KS == 1 || KS == 3) {
+            if constexpr (BM == 64 && BN == 64 && KS == 3 && S == 1) {
+                if (p.wavek == 7) return launch_kernel(k_conv_wavek3<BF16, 7>, p, s);
+                if (p.wavek == 9) return launch_kernel(k_conv_wavek3<BF16, 9>, p, s);
+                if (p.wavek == 12) return launch_kernel(k_conv_wavek3<BF16, 12>, p, s);
+            }
             // all-tap stages exist for the 64x64 tiles the planner gives them to
                 if constexpr (BM == 64 && BN == 64 && KS == 3)
                 if (p.sg == 9) return launch_kernel(k_conv_pipe<BF16, BM, BN, KS, S, 9>, p, s);
