@@ -348,6 +348,278 @@ __global__ __launch_bounds__(kThreads) void k_wgrad16(const uint16_t *__restrict
     }
 }
 
+// ---------------------------------------------------------------- weight gradient, one kernel row
+//
+// Maps whose output divides into 8 x 8 pixel tiles. The general form above loads both
+// operands once per tap and transposes them in registers; here a workgroup owns a 64 x 64
+// (co, ci) tile of a whole kernel row (KW taps) and a run of pixel tiles:
+//  * a tile's 64 output-gradient pixels and the input pixels under them for this kernel
+//    row (8 rows of XC columns; zeros outside the image) go straight from memory to LDS,
+//    128 bytes (64 channels) per pixel, NB tiles deep, one barrier per tile;
+//  * matrix-core fragments want eight pixels of one channel per lane: ds_read_b64_tr_b16
+//    transposes on the way out (16 lanes read 4 pixels x 16 channels and each gets four
+//    pixels of one channel), so a tap is a shift of the row address and nothing is copied.
+//    The order of the pixels within a product is the same for both operands;
+//  * the 32-byte channel pairs of a row are stored at pair ^ f(row), f running over every
+//    second row a read touches: 32 lanes then cover all 64 banks (no conflicts counted);
+//  * two groups of four waves take one half of a tile's pixels each (32 x 32 quadrants),
+//    and read the next tile's fragments while the current one's products run: one wave per
+//    SIMD that waits for its own reads took 0.77 us per tile. The groups exchange halves
+//    through LDS at the end;
+//  * the bias gradient is a product with ones (first ci tile, first kernel row);
+//  * dW and db are added with fp32 atomics (one per element and workgroup).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void dma16(const i32x4 &r, uint32_t lds, int voff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(r) : "memory");
+}
+
+__device__ __forceinline__ i32x4 raw_desc(const void *p, int bytes)
+{
+    const uint64_t u = (uint64_t)p;
+    return i32x4{(int)(uint32_t)u, (int)(uint32_t)(u >> 32), bytes, kBufferFlags};
+}
+
+// Eight pixels of one channel: two transposed reads of four pixels each.
+__device__ __forceinline__ short8 read_tr(const uint8_t *lo, const uint8_t *hi)
+{
+    typedef __attribute__((address_space(3))) s16x4 *lds_p;
+    const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(__attribute__((address_space(3))) uint8_t *)lo);
+    const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_p)(__attribute__((address_space(3))) uint8_t *)hi);
+    return short8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+}
+
+struct WgradRow {
+    int hin, win, cin, hout, wout, cout, pad;
+    int tw, tpi, tiles;                       // pixel tiles per row, per image, in all
+    int ci_tiles, splits, run;                // runs of `run` tiles
+    int x_bytes, g_bytes;
+};
+
+constexpr int kRowThreads = 512;
+
+template <int KW, int S>
+struct WgradShape {
+    static constexpr int ST = KW == 1 ? 1 : S;            // slots between adjacent output pixels
+    static constexpr int XC = 7 * ST + KW;                // staged input columns
+    static constexpr int XI = (8 * XC + 63) / 64;         // input requests per wave (8 rows each)
+    static constexpr int DW = 1 + XI;                     // requests per wave and tile
+    static constexpr int BUF = 8192 + XI * 8192;          // LDS bytes per tile
+    static constexpr int NB = 4;
+    static_assert(NB * BUF <= 128 * 1024 && NB * DW <= 63, "LDS and vmcnt");
+};
+
+template <bool BF16, int KW, int S>
+__global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *__restrict__ x,
+                                                                const uint16_t *__restrict__ g,
+                                                                float *__restrict__ dw, float *__restrict__ db,
+                                                                WgradRow G)
+{
+    using W = WgradShape<KW, S>;
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    // blockIdx.x = ((co tile * ci tiles + ci tile) * KW + kernel row) * splits + run
+    int r = blockIdx.x;
+    const int split = r % G.splits;
+    r /= G.splits;
+    const int ki = r % KW;
+    r /= KW;
+    const int cit = r % G.ci_tiles, cot = r / G.ci_tiles;
+    const int co0 = cot * 64, ci0 = cit * 64;
+    const int t_lo = split * G.run, t_hi = min(G.tiles, t_lo + G.run);
+    const bool has_db = db != nullptr && cit == 0 && ki == 0, bias = has_db && wn == 0;
+    const i32x4 xd = raw_desc(x, G.x_bytes), gd = raw_desc(g, G.g_bytes);
+    const uint32_t lbase = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(uint64_t)(__attribute__((address_space(3))) uint8_t *)smem);
+    // this lane's part of a request of 8 rows: row lane >> 3, 16-byte unit lane & 7 of LDS;
+    // f of its row (8 (wave + 8 v) + (lane >> 3)) does not depend on v
+    const int row8 = 8 * wave + (lane >> 3);
+    const int gu = (lane & 7) ^ (((row8 >> 1) & 3) * 2);
+    const int xu = (lane & 7) ^ (((W::ST == 2 ? row8 >> 2 : row8 >> 1) & 3) * 2);
+    const bool ci_ok = ci0 + xu * 8 < G.cin;
+    // per request: this lane's row and column of the input tile (rows past it: never in the
+    // image) and its byte offset from the tile's first input pixel
+    int xdy[W::XI], xdx[W::XI], xoff[W::XI];
+#pragma unroll
+    for (int v = 0; v < W::XI; ++v) {
+        const int slot = row8 + 64 * v;
+        const int hy = slot / W::XC, hx = slot - hy * W::XC;
+        xdy[v] = ci_ok && hy < 8 ? hy * S : -(1 << 28);
+        xdx[v] = hx * (KW == 1 ? S : 1);
+        xoff[v] = ((hy * S * G.win + xdx[v]) * G.cin + ci0 + xu * 8) * 2;
+    }
+    const int goff = ((wave * G.wout + (lane >> 3)) * G.cout + co0 + gu * 8) * 2;
+    int img = t_lo / G.tpi, ty = (t_lo - img * G.tpi) / G.tw, tx = t_lo - img * G.tpi - ty * G.tw;
+    int left = t_hi - t_lo;                              // tiles not yet requested
+    auto issue = [&](int buf) {                          // past the run: zeros, never used
+        const int gb = ((img * G.hout + ty * 8) * G.wout + tx * 8) * G.cout * 2;
+        dma16(gd, lbase + buf * W::BUF + wave * 1024, left > 0 ? gb + goff : kOutOfRange);
+        const int iy0 = ty * 8 * S - G.pad + ki, ix0 = tx * 8 * S - G.pad;
+        const int xb = ((img * G.hin + iy0) * G.win + ix0) * G.cin * 2;
+#pragma unroll
+        for (int v = 0; v < W::XI; ++v) {
+            const bool ok = left > 0 && (unsigned)(iy0 + xdy[v]) < (unsigned)G.hin &&
+                            (unsigned)(ix0 + xdx[v]) < (unsigned)G.win;
+            dma16(xd, lbase + buf * W::BUF + 8192 + (wave + 8 * v) * 1024, ok ? xb + xoff[v] : kOutOfRange);
+        }
+        --left;
+        if (++tx == G.tw) {
+            tx = 0;
+            if ((++ty) * G.tw == G.tpi) {
+                ty = 0;
+                ++img;
+            }
+        }
+    };
+    // fragment addresses: lane = 16 gq + 4 j + a reads pixel 4 gq + j (of 16), channels 4 a ..;
+    // this group's 32 pixels are tile rows 4 grp .. 4 grp + 3, two halves of 16
+    const int gq = lane >> 4, j = (lane >> 2) & 3, ac = lane & 3;
+    int ga[2], xa[KW][2];                                // [half], [tap][half]: channel pairs 2 wm, 2 wn
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int p = grp * 32 + h * 16 + 4 * gq + j;
+        ga[h] = p * 128 + ((wm * 2) ^ ((p >> 1) & 3)) * 32 + ac * 8;
+#pragma unroll
+        for (int kj = 0; kj < KW; ++kj) {
+            const int slot = (p >> 3) * W::XC + (p & 7) * W::ST + kj;
+            const int f = (W::ST == 2 ? slot >> 2 : slot >> 1) & 3;
+            xa[kj][h] = 8192 + slot * 128 + ((wn * 2) ^ f) * 32 + ac * 8;
+        }
+    }
+    auto read_g = [&](const uint8_t *b, int mi) { return read_tr(b + (ga[0] ^ (mi * 32)), b + (ga[1] ^ (mi * 32))); };
+    auto read_x = [&](const uint8_t *b, int kj, int ni) {
+        return read_tr(b + (xa[kj][0] ^ (ni * 32)), b + (xa[kj][1] ^ (ni * 32)));
+    };
+    f32x4 acc[KW][2][2], accb[2];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) {
+        accb[mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kj = 0; kj < KW; ++kj)
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni) acc[kj][mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const short one = BF16 ? (short)0x3F80 : (short)0x3C00;
+    const short8 ones = {one, one, one, one, one, one, one, one};
+
+    // Tile t + 1 has arrived for this wave and its reads of tile t are done; past the
+    // barrier both hold for every wave, so tile t's buffer takes tile t + NB.
+    auto arrived = [&](auto n) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(decltype(n)::value) : "memory");
+    };
+#pragma unroll
+    for (int d = 0; d < W::NB; ++d) issue(d);
+    arrived(std::integral_constant<int, (W::NB - 1) * W::DW>{});
+    short8 af[2], bf[KW][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) af[i] = read_g(smem, i);
+#pragma unroll
+    for (int kj = 0; kj < KW; ++kj)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) bf[kj][i] = read_x(smem, kj, i);
+    int buf = 0;
+    for (int t = t_lo; t < t_hi; ++t) {
+        arrived(std::integral_constant<int, (W::NB - 2) * W::DW>{});
+        const int next = buf + 1 == W::NB ? 0 : buf + 1;
+        const uint8_t *b = smem + next * W::BUF;         // past the run: the zeros requested there
+        short8 an[2], bn[KW][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) an[i] = read_g(b, i);
+#pragma unroll
+        for (int kj = 0; kj < KW; ++kj) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) bn[kj][i] = read_x(b, kj, i);
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) acc[kj][mi][ni] = mfma<BF16>(af[mi], bf[kj][ni], acc[kj][mi][ni]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (bias) {
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) accb[mi] = mfma<BF16>(af[mi], ones, accb[mi]);
+        }
+        issue(buf);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            af[i] = an[i];
+#pragma unroll
+            for (int kj = 0; kj < KW; ++kj) bf[kj][i] = bn[kj][i];
+        }
+        buf = next;
+    }
+    // every request must be done before LDS is used for the exchange (and given back)
+    arrived(std::integral_constant<int, 0>{});
+    // The tile [tap][co][ci] in LDS: the second group's sums, then the first's added
+    // (first half of the pixels + second half, per element).
+    // acc[kj][mi][ni][i]: co = wm*32 + mi*16 + (lane>>4)*4 + i, ci = wn*32 + ni*16 + (lane&15)
+    float *out = (float *)smem;
+    float *sum = out + KW * 64 * 64;                     // [group][64]
+    const int oo = (wm * 32 + (lane >> 4) * 4) * 64 + wn * 32 + (lane & 15);
+    if (grp == 1) {
+#pragma unroll
+        for (int kj = 0; kj < KW; ++kj)
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) out[oo + (kj * 64 + mi * 16 + i) * 64 + ni * 16] = acc[kj][mi][ni][i];
+    }
+    if (bias && (lane & 15) == 0) {                      // every column holds the sum
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum[grp * 64 + wm * 32 + mi * 16 + (lane >> 4) * 4 + i] = accb[mi][i];
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+        for (int kj = 0; kj < KW; ++kj)
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float *o = &out[oo + (kj * 64 + mi * 16 + i) * 64 + ni * 16];
+                        *o = acc[kj][mi][ni][i] + *o;
+                    }
+    }
+    __syncthreads();
+    // One add covers 64 consecutive ci of a (tap, co) row; every run starts at another row,
+    // so that runs which end together do not queue at the same addresses.
+    const int rowb = KW * KW * G.cin * 4;
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(dw + ((size_t)co0 * KW + ki) * KW * G.cin + ci0), (short)0, kOutOfRange, kBufferFlags);
+    const int lo = ci0 + lane < G.cin ? lane * 4 : kOutOfRange;
+#pragma unroll 8
+    for (int it = 0; it < KW * 8; ++it) {
+        const int row = (it * 8 + wave + split * 24) % (KW * 64);      // uniform
+        __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(out[row * 64 + lane], rw, lo,
+                                                        (row & 63) * rowb + (row >> 6) * G.cin * 4, 0);
+    }
+    if (has_db && wave == 0) unsafeAtomicAdd(&db[co0 + lane], sum[lane] + sum[64 + lane]);
+}
+
+template <bool BF16, int KW, int S>
+hipError_t launch_wgrad_row(const uint16_t *x, const uint16_t *g, float *dw, float *db, const WgradRow &G,
+                            unsigned grid, hipStream_t s)
+{
+    constexpr int lds = WgradShape<KW, S>::NB * WgradShape<KW, S>::BUF;
+    auto kern = k_wgrad_row16<BF16, KW, S>;
+    if (lds > 60 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowThreads), lds, s, x, g, dw, db, G);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- RMSprop
 
 template <bool BF16>
@@ -503,6 +775,42 @@ hipError_t launch_conv_input_grad(const uint16_t *grad_out, const uint16_t *w, c
 hipError_t launch_conv_weight_grad(const uint16_t *x, const uint16_t *g, float *dw, float *db,
                                    const LayerGeom &fwd, bool bf16, hipStream_t s)
 {
+    // One kernel row per workgroup where the output divides into 8 x 8 tiles (us per launch,
+    // before -> with it: 3x3 64 -> 64 at 128 x 256 23.2 -> 16.6, 128 -> 128 at 64 x 128 19.6
+    // -> 16.0, 32 -> 64 stride 2 20.7 -> 15.6; 1x1 64 -> 128 13.9 -> 7.0), not for 3x3 layers
+    // below 1024 output pixels (8 x 16 pixels 4.8 -> 6.1), nor where the uniform offsets of
+    // a 64-row tile could pass 2 GiB.
+    if (fwd.hout % 8 == 0 && fwd.wout % 8 == 0 && fwd.cin <= (1 << 18) &&
+        (fwd.kh == 1 || fwd.n * fwd.hout * fwd.wout >= 1024)) {
+        WgradRow R;
+        R.hin = fwd.hin; R.win = fwd.win; R.cin = fwd.cin;
+        R.hout = fwd.hout; R.wout = fwd.wout; R.cout = fwd.cout; R.pad = fwd.pad;
+        R.tw = fwd.wout / 8;
+        R.tpi = (fwd.hout / 8) * R.tw;
+        R.tiles = fwd.n * R.tpi;
+        R.ci_tiles = (fwd.cin + 63) / 64;
+        const int base = (fwd.cout / 64) * R.ci_tiles * fwd.kh;
+        // About 128 workgroups: fewer leave CUs idle, more add to the same addresses more
+        // often (64 -> 64, 3x3, 128 x 256 pixels: 21.0 us with 63 workgroups, 16.6 with 126,
+        // 18.3 with 255).
+        int splits = base >= 128 ? 1 : 128 / base;
+        if (splits > R.tiles) splits = R.tiles;
+        R.run = (R.tiles + splits - 1) / splits;
+        R.splits = (R.tiles + R.run - 1) / R.run;
+        R.x_bytes = (int)((size_t)fwd.n * fwd.hin * fwd.win * fwd.cin * 2);
+        R.g_bytes = (int)((size_t)fwd.n * fwd.hout * fwd.wout * fwd.cout * 2);
+        const unsigned grid = (unsigned)(base * R.splits);
+        auto go = [&](auto kw, auto st) {
+            constexpr int KW = decltype(kw)::value, S = decltype(st)::value;
+            return bf16 ? launch_wgrad_row<true, KW, S>(x, g, dw, db, R, grid, s)
+                        : launch_wgrad_row<false, KW, S>(x, g, dw, db, R, grid, s);
+        };
+        using one = std::integral_constant<int, 1>;
+        using two = std::integral_constant<int, 2>;
+        using three = std::integral_constant<int, 3>;
+        if (fwd.kh == 1) return fwd.stride == 1 ? go(one{}, one{}) : go(one{}, two{});
+        return fwd.stride == 1 ? go(three{}, one{}) : go(three{}, two{});
+    }
     WgradGeom G;
     G.n = fwd.n; G.hin = fwd.hin; G.win = fwd.win; G.cin = fwd.cin;
     G.hout = fwd.hout; G.wout = fwd.wout; G.cout = fwd.cout;

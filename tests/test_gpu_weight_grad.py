@@ -1,0 +1,65 @@
+"""Weight and bias gradients at the edges of the kernel-row form (output maps that divide
+into 8 x 8 tiles): one and many tiles per run, ragged input channels, both strides and
+kernel sizes, batches, both formats, and the sizes just below its range. Small integers
+make every product and sum exact in fp32, so the comparison is exact and the order of the
+atomic additions does not matter."""
+import numpy as np
+import pytest
+
+import synth
+from _util import to_dev
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# n, cin, cout, k, stride, hout, wout, dtype, bias
+CASES = [
+    (1, 64, 64, 3, 1, 32, 32, "bf16", True),      # 16 tiles: the smallest 3x3 map
+    (1, 64, 64, 3, 1, 24, 40, "bf16", True),      # 960 pixels: the general form
+    (2, 72, 128, 3, 1, 24, 24, "f16", True),      # ragged second ci tile, two images
+    (1, 8, 64, 3, 2, 32, 40, "bf16", False),      # eight input channels, stride 2
+    (3, 136, 64, 3, 2, 16, 24, "bf16", True),     # a run that crosses images
+    (1, 64, 64, 1, 1, 8, 8, "bf16", True),        # one tile
+    (1, 200, 192, 1, 2, 16, 8, "f16", True),
+    (1, 64, 64, 3, 1, 128, 64, "bf16", True),     # several tiles per run, a shorter last run
+    (1, 256, 256, 3, 1, 32, 32, "bf16", True),    # as many tiles of (co, ci) as workgroups
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=["_".join(map(str, c)) for c in CASES])
+def test_weight_grad_integer_exact(case):
+    from paper_2108_09376_amd import bc
+    n, cin, cout, k, s, h, w, dt, bias = case
+    r = synth.rng(7500 + cin + cout + h)
+    x = synth.small_ints(r, (n, cin, h * s, w * s), -2, 2)
+    g = synth.small_ints(r, (n, cout, h, w), -2, 2)
+    xp = np.pad(x, ((0, 0), (0, 0), (k // 2, k // 2), (k // 2, k // 2))).astype(np.float64)
+    gf = g.astype(np.float64).transpose(1, 0, 2, 3).reshape(cout, -1)
+    want = np.empty((cout, k, k, cin))
+    for i in range(k):
+        for j in range(k):
+            t = xp[:, :, i:i + s * (h - 1) + 1:s, j:j + s * (w - 1) + 1:s]
+            want[:, i, j] = gf @ t.transpose(1, 0, 2, 3).reshape(cin, -1).T
+    dw0 = synth.small_ints(r, (cout, k, k, cin))
+    dw = torch.from_numpy(dw0.copy()).cuda()
+    db = torch.full((cout,), 3.0, device="cuda") if bias else None
+    print("weight gradient", case, flush=True)
+    bc.bc_conv2d_weight_grad((k, k, s, k // 2, 0), to_dev(synth.to_storage_bits(x, dt), dt),
+                             to_dev(synth.to_storage_bits(g, dt), dt), dw, db)
+    torch.cuda.synchronize()
+    assert np.array_equal(dw.cpu().numpy(), (want + dw0).astype(np.float32))
+    if bias:
+        assert np.array_equal(db.cpu().numpy(), (gf.sum(1) + 3.0).astype(np.float32))
+
+
+def test_weight_grad_outside_values_stay_out():
+    """Padding is zero and pixels that a tap does not reach do not enter its sum: an
+    infinity in the last input column reaches only the taps that read that column."""
+    from paper_2108_09376_amd import bc
+    x = torch.ones((1, 32, 32, 64), dtype=torch.bfloat16, device="cuda")
+    x[0, :, 31, 5] = float("inf")
+    g = torch.ones((1, 32, 32, 64), dtype=torch.bfloat16, device="cuda")
+    dw = torch.zeros((64, 3, 3, 64), device="cuda")
+    bc.bc_conv2d_weight_grad((3, 3, 1, 1, 0), x, g, dw, None)
+    bad = ~torch.isfinite(dw)
+    assert bool(bad[:, :, 1:, 5].all()) and int(bad.sum()) == 64 * 3 * 2
