@@ -97,6 +97,7 @@ struct MfmaArgs {
     FastDiv f_hrhc, f_hc, f_rbw, f_bw;  // divisions by HR*HC, HC, R*bw, bw
     int ksplit, cps;                    // K slices per tile, 32-channel chunks per slice
     int kseq;                           // wave-K form: slices one workgroup runs in order
+    int perm8;                          // wave-K form: rows permuted for 8-pixel-wide blocks
     int tiles_full;                     // tiles (incl. K slices) of a full frame
     int slots;                          // stem form: workgroups resident on the device
     int xu, gx;                         // XCD grouping of the tile order (xcd_tile), 0 = off
@@ -200,7 +201,11 @@ __device__ __forceinline__ bool load_tile_blocks(const MfmaArgs &a, int mt, Tile
 // the storage format and writes with 16-byte buffer stores; rows of inactive patches
 // use an out-of-range offset, which the hardware drops. `tid` is the thread's index in
 // its group of four waves; a group that is not `live` only takes the barriers.
-template <bool BF16, int BM, int BN>
+// PERM: the rows of a 64-row tile of one 8-pixel-wide block may be permuted (a.perm8): row
+// 16 mi + 8 h + c of the tile is pixel row mi + 4 h, column c of the block.
+__device__ __forceinline__ int perm8_row(int m) { return (((m >> 4) + 4 * ((m >> 3) & 1)) << 3) + (m & 7); }
+
+template <bool BF16, int BM, int BN, bool PERM = false>
 struct Epilogue {
     static constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 16;
     static constexpr int NP = WN / 32, NU = WM / 16;
@@ -225,7 +230,8 @@ struct Epilogue {
         const int rbw = a.R * a.bw;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
-            const int m = wm * WM + (lane >> 2) + 16 * u;
+            int m = wm * WM + (lane >> 2) + 16 * u;
+            if constexpr (PERM) m = a.perm8 ? perm8_row(m) : m;
             const int p = fdiv(m, a.f_rbw);
             const int local = m - p * rbw;
             const int pr = fdiv(local, a.f_bw), pc = local - pr * a.bw;
@@ -876,7 +882,11 @@ __global__ __launch_bounds__(kThreads) void k_conv_pipe_pair(MfmaArgs a1, MfmaAr
 //    tap), and reads the next tap's fragments while the current tap's products run;
 //  * a row (pixel slot or output channel) is 64 bytes, its 16-byte quarter q stored at
 //    q ^ ((row >> 1) & 3): the loads write 1 KB linearly, so the swizzle is in which
-//    quarter a lane requests, and eight consecutive rows read at one quarter use all banks.
+//    quarter a lane requests, and sixteen consecutive rows read at one quarter use all 64
+//    banks (no conflicts counted; >> 2 in its place: 3.6 of 7.3 cycles per read). Of an
+//    8-pixel-wide block a fragment takes pixel rows r and r + 4 (perm8): with halo rows of
+//    10 slots these are 40 slots apart, which is conflict free too, and adjacent rows, 10
+//    slots apart, are not (3.6 of 7.3 cycles).
 // The four partial tiles are added through LDS in wave order, wave w finishing quadrant w.
 // The order of the sums depends on the layer's shape only.
 
@@ -959,7 +969,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv_wavek3(MfmaArgs a)
     const int nt = mn % a.ntn, mt = mn / a.ntn;
     const int n0 = nt * 64;
     if (!load_tile_blocks(a, mt, tb)) return;   // tile beyond the active count (uniform)
-    Epilogue<BF16, 64, 64> epi;
+    Epilogue<BF16, 64, 64, true> epi;
     epi.prefetch(a, tb, n0);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1002,7 +1012,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv_wavek3(MfmaArgs a)
     const int rbw = a.R * a.bw;
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi) {
-        const int m = mi * 16 + (lane & 15);
+        const int r = mi * 16 + (lane & 15);
+        const int m = a.perm8 ? perm8_row(r) : r;
         const int p = fdiv(m, a.f_rbw);
         const int local = m - p * rbw;
         const int pr = fdiv(local, a.f_bw), pc = local - pr * a.bw;
@@ -1436,6 +1447,7 @@ bool make_plan(const LayerGeom &g, int BM, int BN, Plan &pl)
     const int KS = g.kh, S = g.stride;
     a.ksplit = 1;
     a.kseq = 1;
+    a.perm8 = 0;
     a.cps = (g.cin + BK - 1) / BK;
     pl.ws_bytes = 0;
     if (g.cin % 8) {
@@ -1572,6 +1584,7 @@ bool choose_plan(const LayerGeom &g, Plan &best)
                     best.grid = tiles;
                 }
                 best.wavek = a.nslot <= 112 ? 7 : a.nslot <= 144 ? 9 : 12;
+                a.perm8 = a.P == 1 && g.bw == 8 && a.R == 8;
                 best.lds = 4 * (size_t)wavek3_bytes(best.wavek, wavek3_depth(best.wavek));
             }
             // 1x1 layers with 64x64 tiles stage two chunks per barrier (a same-process A/B
