@@ -1026,7 +1026,7 @@ bc_status bc_rmsprop_step_many(const bc_param *params, int32_t n, float lr, floa
         m.w16[t] = (uint16_t *)p.w16;
         m.count[t] = p.count;
         m.first[t] = (int)blocks;
-        blocks += (p.count + 255) / 256;
+        blocks += (p.count + bc::kRmspropElems - 1) / bc::kRmspropElems;
     }
     m.first[n] = (int)blocks;
     if (any16 && dtype != BC_BF16 && dtype != BC_F16) return fail(BC_ERR_DTYPE, "the copies must be bf16 or f16");

@@ -127,8 +127,9 @@ hipError_t launch_conv_input_grad(const uint16_t *grad_out, const uint16_t *w, c
 hipError_t launch_conv_weight_grad(const uint16_t *x, const uint16_t *g, float *dw, float *db,
                                    const LayerGeom &fwd, bool bf16, hipStream_t s);
 // Multi-tensor RMSprop: up to kMaxParams tensors; first[t] is the first workgroup of
-// tensor t (first[n] = the grid), each workgroup covering 256 elements.
+// tensor t (first[n] = the grid), each workgroup covering kRmspropElems elements.
 constexpr int kMaxParams = 64;
+constexpr int kRmspropElems = 1024;
 struct RmspropMany {
     float *w[kMaxParams], *v[kMaxParams], *grad[kMaxParams];
     uint16_t *w16[kMaxParams];

@@ -642,25 +642,40 @@ __global__ __launch_bounds__(kThreads) void k_rmsprop(float *__restrict__ w, flo
 
 // Several tensors in one launch: workgroup b belongs to the tensor t with
 // first[t] <= b < first[t + 1] (a uniform scan over at most kMaxParams entries of the
-// kernel arguments), element (b - first[t]) * kThreads + thread of that tensor.
+// kernel arguments), elements [(b - first[t]) * kRmspropElems, ...) of that tensor, four per
+// thread and all requested before the first is used (1.4 M parameters: 12.8 -> 8.2 us).
 template <bool BF16>
 __global__ __launch_bounds__(kThreads) void k_rmsprop_many(RmspropMany m, float lr, float alpha,
                                                            float eps, float wd)
 {
+    constexpr int U = kRmspropElems / kThreads;
     const int b = blockIdx.x;
     int t = 0;
     while (t + 1 < m.n && m.first[t + 1] <= b) ++t;
-    const long long i = (long long)(b - m.first[t]) * kThreads + threadIdx.x;
-    if (i >= m.count[t]) return;
+    const long long i0 = (long long)(b - m.first[t]) * kRmspropElems + threadIdx.x;
     float *w = m.w[t], *v = m.v[t], *grad = m.grad[t];
-    const float wi = w[i];
-    const float gi = grad[i] + wd * wi;
-    const float vi = alpha * v[i] + (1.f - alpha) * gi * gi;
-    const float wn = wi - lr * gi / (sqrtf(vi) + eps);
-    v[i] = vi;
-    w[i] = wn;
-    grad[i] = 0.f;
-    if (m.w16[t]) m.w16[t][i] = (uint16_t)f32_to_h16<BF16>(wn);
+    const long long count = m.count[t];
+    if (i0 >= count) return;
+    float wi[U], vo[U], go[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const long long i = i0 + u * kThreads < count ? i0 + u * kThreads : i0;
+        wi[u] = w[i];
+        vo[u] = v[i];
+        go[u] = grad[i];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const long long i = i0 + u * kThreads;
+        if (i >= count) continue;
+        const float gi = go[u] + wd * wi[u];
+        const float vi = alpha * vo[u] + (1.f - alpha) * gi * gi;
+        const float wn = wi[u] - lr * gi / (sqrtf(vi) + eps);
+        v[i] = vi;
+        w[i] = wn;
+        grad[i] = 0.f;
+        if (m.w16[t]) m.w16[t][i] = (uint16_t)f32_to_h16<BF16>(wn);
+    }
 }
 
 // ---------------------------------------------------------------- workspace

@@ -63,3 +63,24 @@ def test_weight_grad_outside_values_stay_out():
     bc.bc_conv2d_weight_grad((3, 3, 1, 1, 0), x, g, dw, None)
     bad = ~torch.isfinite(dw)
     assert bool(bad[:, :, 1:, 5].all()) and int(bad.sum()) == 64 * 3 * 2
+
+
+@pytest.mark.parametrize("counts", [(1, 255, 1024, 1025), (4096, 2049, 3)])
+def test_rmsprop_many_elements_per_workgroup(counts):
+    """Tensors that end inside, at and just past a workgroup's 1024 elements take the same
+    step as one by one, byte for byte, with and without a 16-bit copy."""
+    from paper_2108_09376_amd import bc
+    r = synth.rng(7700 + len(counts))
+    make = lambda: [tuple(torch.from_numpy(a).cuda() for a in t) for t in data]
+    data = [(synth.normal(r, n), np.abs(synth.normal(r, n)), synth.normal(r, n)) for n in counts]
+    many, single = make(), make()
+    c16 = [torch.zeros(n, dtype=torch.bfloat16, device="cuda") if i % 2 else None for i, n in enumerate(counts)]
+    s16 = [None if c is None else c.clone() for c in c16]
+    bc.bc_rmsprop_step_many([(w, v, g, c) for (w, v, g), c in zip(many, c16)], 1e-2, 0.9, 1e-8, 1e-3)
+    for (w, v, g), c in zip(single, s16):
+        bc.bc_rmsprop_step(w, v, g, 1e-2, 0.9, 1e-8, 1e-3, c)
+    torch.cuda.synchronize()
+    for a, b in zip(many, single):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+    for a, b in zip(c16, s16):
+        assert a is None or torch.equal(a, b)
