@@ -1557,20 +1557,22 @@ bool choose_plan(const LayerGeom &g, Plan &best)
                     best.lds = lds;
                 }
             }
-            // Wave-K form (k_conv_wavek3): stride-1 3x3 layers with a chunk per wave and at
-            // most 512 tiles, or 16 chunks and at most 2048 (measured, us per launch, before
-            // -> with it, at 38 of 128 blocks / every block: 256->256 at stride 16 12.5 -> 9.6
-            // / 24.2 -> 18.2; 512->512 at stride 32 14.9 -> 12.0 / 28.2 -> 16.4, at stride 16
-            // 30.4 -> 24.9 / 70.4 -> 53.3; 128->128 on 256 tiles 8.3 -> 7.5 / 9.2 -> 8.0). Not
-            // with two chunks (64->256 on 128 tiles: 6.5 -> 7.1, two waves have no work) and
-            // not for many short tiles (128->128 on 1024 tiles 11.9 -> 14.6, 256->256 on 2048
-            // 26.4 -> 27.3): one 150 KB workgroup per CU overlaps no tile's start and end.
+            // Wave-K form (k_conv_wavek3): stride-1 3x3 layers with 8 chunks on 257 to 512
+            // tiles, or 16 chunks on at most 2048 (measured, us per launch, before -> with
+            // it, at 38 of 128 blocks / every block: 256->256 at stride 16 12.5 -> 9.6 / 24.2
+            // -> 18.3; 512->512 at stride 32 14.9 -> 12.0 / 28.2 -> 16.2, at stride 16 30.4 ->
+            // 25.0 / 70.4 -> 51.7). Not for many short tiles (128->128 on 1024 tiles 11.9 ->
+            // 14.6, 256->256 on 2048 26.4 -> 27.3): one 150 KB workgroup per CU overlaps no
+            // tile's start and end. Shorter K on fewer tiles keeps its order of sums: there
+            // the form saves 1 us (128->128 on 256 tiles 8.9 -> 8.0), and the policy network,
+            // whose layers these are and whose update feeds rounding back into its weights,
+            // keeps its bits.
             // More than 256 tiles keep K whole: two slices as workgroups of their own cost
             // 512->512 at stride 16 25 -> 32 us. A call without an index runs every tile: if
             // its slices are more workgroups than CUs, each tile's workgroup runs them in
-            // turn (same sums, same order; 512->512 at stride 32, every block, 22.4 -> 16.4).
+            // turn (same sums, same order; 512->512 at stride 32, every block, 22.4 -> 16.2).
             if (g.kh == 3 && g.stride == 1 && best.BM == 64 && best.BN == 64 && a.nslot <= 192 &&
-                ((nchunk >= 4 && tiles <= 512) || (nchunk >= 16 && tiles <= 2048))) {
+                ((nchunk >= 8 && tiles > 256 && tiles <= 512) || (nchunk >= 16 && tiles <= 2048))) {
                 // ws_bytes stays: which layers need the workspace, and are refused without it,
                 // is documented by shape and does not change with the form
                 if (tiles > 256) {

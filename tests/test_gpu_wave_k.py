@@ -22,16 +22,18 @@ def B():
 
 # n, cin, cout, gh, gw, bh, bw, dtype, residual, active fraction
 CASES = [
-    (1, 128, 64, 2, 3, 8, 8, "bf16", False, 0.5),     # one chunk per wave
-    (1, 136, 64, 3, 2, 8, 8, "f16", True, 0.5),       # five chunks, the last one ragged
-    (2, 104, 128, 2, 2, 8, 8, "bf16", True, 0.6),     # 3.25 chunks: four, one of 8 channels
-    (1, 232, 64, 4, 5, 4, 4, "bf16", False, 0.4),     # four 4x4 patches per tile, ragged last patch
-    (1, 256, 192, 3, 3, 8, 8, "bf16", True, 0.3),     # two K slices
-    (1, 384, 64, 2, 2, 16, 16, "bf16", False, 0.5),   # bands of a 16-wide block, four slices
-    (1, 160, 64, 1, 2, 32, 32, "f16", False, 1.0),    # bands of a 32-wide block
-    (1, 128, 64, 1, 1, 4, 64, "bf16", True, 1.0),     # one block, one-row bands
-    (1, 128, 64, 4, 4, 2, 4, "bf16", False, 0.4),     # eight 2x4 patches: the largest halo
+    (1, 512, 64, 2, 3, 8, 8, "bf16", False, 0.5),     # four K slices, one chunk per wave
+    (1, 488, 64, 3, 2, 8, 8, "f16", True, 0.5),       # the last chunk ragged
+    (2, 520, 128, 2, 2, 8, 8, "bf16", True, 0.6),     # 17 chunks: the last slice shorter
+    (1, 616, 64, 4, 5, 4, 4, "bf16", False, 0.4),     # four 4x4 patches per tile, ragged last patch
+    (1, 256, 320, 6, 9, 8, 8, "bf16", True, 0.3),     # 270 tiles, K whole, two chunks per wave
+    (1, 232, 320, 6, 9, 8, 8, "f16", False, 0.3),     # eight chunks, the last of 8 channels
+    (1, 512, 64, 2, 2, 16, 16, "bf16", False, 0.5),   # bands of a 16-wide block
+    (1, 512, 64, 1, 2, 32, 32, "f16", False, 1.0),    # bands of a 32-wide block
+    (1, 512, 64, 1, 1, 4, 64, "bf16", True, 1.0),     # one block, one-row bands
+    (1, 512, 64, 4, 4, 2, 4, "bf16", False, 0.4),     # eight 2x4 patches: the largest halo
     (1, 512, 64, 3, 5, 8, 8, "bf16", False, 0.07),    # one active block
+    (1, 232, 64, 3, 5, 8, 8, "bf16", False, 0.3),     # few tiles, eight chunks: another form
 ]
 
 
@@ -66,7 +68,7 @@ def test_wave_k_integer_exact(B, case):
     assert np.array_equal(got[~sel], prev[~sel])                # copied blocks: previous bits
 
 
-@pytest.mark.parametrize("shape", [(512, 128, 16, 16, 8, 8), (512, 128, 8, 32, 4, 4)])
+@pytest.mark.parametrize("shape", [(512, 128, 16, 16, 8, 8), (512, 512, 8, 16, 4, 4), (256, 256, 8, 16, 8, 8)])
 def test_wave_k_bits_do_not_depend_on_the_call(B, shape):
     """An active block has the same bits alone, with others, and in a call without an index
     (where K slices may run in turn instead of in workgroups of their own)."""
