@@ -12,7 +12,8 @@
 //    onto the even pixels of a map of the input's size (zeros between), then a
 //    stride-1 convolution with padding k/2 (these two kernels are here);
 //  * weight gradient: dW[co][i][j][ci] += sum_p G[p][co] X[p*s - pad + (i, j)][ci], an
-//    implicit GEMM whose reduction runs over pixels. A workgroup owns a 64 x 64
+//    implicit GEMM whose reduction runs over pixels (maps that divide into 8 x 8 tiles:
+//    k_wgrad_row16; the rest, here:). A workgroup owns a 64 x 64
 //    (co, ci) tile of one tap and a range of 1024 pixels; per 128-pixel chunk it loads
 //    G and the tap-shifted X rows with 16-byte requests (eight channels of one pixel),
 //    transposes them in registers and stores them in LDS as [channel][pixel], so that
