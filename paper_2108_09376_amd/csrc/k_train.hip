@@ -29,6 +29,8 @@
 //    (1 - alpha) g'^2; w -= lr g' / (sqrt(v) + eps); the gradient is reset to 0 and the
 //    16-bit copy of w rewritten (round to nearest even); for one tensor, or for up to
 //    kMaxParams tensors in one launch (their pointers and sizes in the kernel arguments).
+#include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -367,8 +369,10 @@ __global__ __launch_bounds__(kThreads) void k_wgrad16(const uint16_t *__restrict
 //    and read the next tile's fragments while the current one's products run: one wave per
 //    SIMD that waits for its own reads took 0.77 us per tile. The groups exchange halves
 //    through LDS at the end;
-//  * the bias gradient is a product with ones (first ci tile, first kernel row);
-//  * dW and db are added with fp32 atomics (one per element and workgroup).
+//  * products of at most kFold tiles are added up by the matrix cores, whose running sums
+//    round less well than fp32 additions do; then they join the run's totals;
+//  * dW is added with fp32 atomics (one per element and workgroup);
+//  * the bias gradient has workgroups of its own at the end of the grid (bias_run).
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void dma16(const i32x4 &r, uint32_t lds, int voff)
@@ -396,10 +400,53 @@ struct WgradRow {
     int hin, win, cin, hout, wout, cout, pad;
     int tw, tpi, tiles;                       // pixel tiles per row, per image, in all
     int ci_tiles, splits, run;                // runs of `run` tiles
+    int npix, wgs;                            // output pixels; workgroups of dW (db's follow)
+    int bias_px, bias_runs;                   // pixels per workgroup of db, workgroups per co tile
     int x_bytes, g_bytes;
 };
 
 constexpr int kRowThreads = 512;
+constexpr int kFold = 16;
+
+// Adds the gradients of 64 output channels (from co0) over the pixels [p_lo, p_hi) to db.
+// Of every kBiasPx pixels a thread sums sixteen (requested together) for eight channels;
+// the 64 threads of a channel then meet in a tree through LDS (18 KB), one atomic each.
+constexpr int kBiasPx = 1024;
+
+template <bool BF16>
+__device__ __forceinline__ void bias_run(const __amdgpu_buffer_rsrc_t &rg, float *db, int cout, int co0, int p_lo,
+                                         int p_hi, float *part)
+{
+    constexpr int N = kBiasPx / 64;
+    const int tid = threadIdx.x, cv = tid & 7, pq = tid >> 3;
+    float tot[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int p0 = p_lo + pq; p0 - pq < p_hi; p0 += kBiasPx) {
+        i32x4 v[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            v[i] = __builtin_amdgcn_raw_buffer_load_b128(
+                rg, p0 + 64 * i < p_hi ? ((p0 + 64 * i) * cout + co0 + cv * 8) * 2 : kOutOfRange, 0, 0);
+        float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                sum[e] += h16_to_f32<BF16>(((uint32_t)v[i][e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) tot[e] += sum[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part[pq * 64 + cv * 8 + e] = tot[e];
+    __syncthreads();
+    auto eight = [](const float *p) {
+        return ((p[0] + p[64]) + (p[128] + p[192])) + ((p[256] + p[320]) + (p[384] + p[448]));
+    };
+    const int ch = tid & 63;
+    float *joined = part + 64 * 64;
+    joined[(tid >> 6) * 64 + ch] = eight(part + (tid >> 6) * 512 + ch);
+    __syncthreads();
+    if (tid < 64) unsafeAtomicAdd(&db[co0 + ch], eight(joined + ch));
+}
 
 template <int KW, int S>
 struct WgradShape {
@@ -423,6 +470,14 @@ __global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    if ((int)blockIdx.x >= G.wgs) {                      // db (uniform)
+        const int b = blockIdx.x - G.wgs, cot = b / G.bias_runs;
+        const int p_lo = (b - cot * G.bias_runs) * G.bias_px;
+        const __amdgpu_buffer_rsrc_t rg = __builtin_amdgcn_make_buffer_rsrc((void *)g, (short)0, G.g_bytes,
+                                                                            kBufferFlags);
+        bias_run<BF16>(rg, db, G.cout, cot * 64, p_lo, min(G.npix, p_lo + G.bias_px), (float *)smem);
+        return;
+    }
     // blockIdx.x = ((co tile * ci tiles + ci tile) * KW + kernel row) * splits + run
     int r = blockIdx.x;
     const int split = r % G.splits;
@@ -432,7 +487,6 @@ __global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *
     const int cit = r % G.ci_tiles, cot = r / G.ci_tiles;
     const int co0 = cot * 64, ci0 = cit * 64;
     const int t_lo = split * G.run, t_hi = min(G.tiles, t_lo + G.run);
-    const bool has_db = db != nullptr && cit == 0 && ki == 0, bias = has_db && wn == 0;
     const i32x4 xd = raw_desc(x, G.x_bytes), gd = raw_desc(g, G.g_bytes);
     const uint32_t lbase = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uint64_t)(__attribute__((address_space(3))) uint8_t *)smem);
@@ -495,17 +549,13 @@ __global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *
     auto read_x = [&](const uint8_t *b, int kj, int ni) {
         return read_tr(b + (xa[kj][0] ^ (ni * 32)), b + (xa[kj][1] ^ (ni * 32)));
     };
-    f32x4 acc[KW][2][2], accb[2];
+    f32x4 acc[KW][2][2], tot[KW][2][2];                  // tot: of the batches before, if any
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi) {
-        accb[mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int kj = 0; kj < KW; ++kj)
 #pragma unroll
-        for (int kj = 0; kj < KW; ++kj)
+        for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
             for (int ni = 0; ni < 2; ++ni) acc[kj][mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    const short one = BF16 ? (short)0x3F80 : (short)0x3C00;
-    const short8 ones = {one, one, one, one, one, one, one, one};
 
     // Tile t + 1 has arrived for this wave and its reads of tile t are done; past the
     // barrier both hold for every wave, so tile t's buffer takes tile t + NB.
@@ -523,35 +573,54 @@ __global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *
 #pragma unroll
         for (int i = 0; i < 2; ++i) bf[kj][i] = read_x(smem, kj, i);
     int buf = 0;
-    for (int t = t_lo; t < t_hi; ++t) {
-        arrived(std::integral_constant<int, (W::NB - 2) * W::DW>{});
-        const int next = buf + 1 == W::NB ? 0 : buf + 1;
-        const uint8_t *b = smem + next * W::BUF;         // past the run: the zeros requested there
-        short8 an[2], bn[KW][2];
+    bool folded = false;
+    for (int t = t_lo;;) {
+        const int t_fold = min(t_hi, t + kFold);
+        for (; t < t_fold; ++t) {
+            arrived(std::integral_constant<int, (W::NB - 2) * W::DW>{});
+            const int next = buf + 1 == W::NB ? 0 : buf + 1;
+            const uint8_t *b = smem + next * W::BUF;     // past the run: the zeros requested there
+            short8 an[2], bn[KW][2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) an[i] = read_g(b, i);
+            for (int i = 0; i < 2; ++i) an[i] = read_g(b, i);
 #pragma unroll
-        for (int kj = 0; kj < KW; ++kj) {
+            for (int kj = 0; kj < KW; ++kj) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) bn[kj][i] = read_x(b, kj, i);
+                for (int i = 0; i < 2; ++i) bn[kj][i] = read_x(b, kj, i);
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni) acc[kj][mi][ni] = mfma<BF16>(af[mi], bf[kj][ni], acc[kj][mi][ni]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            issue(buf);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                af[i] = an[i];
+#pragma unroll
+                for (int kj = 0; kj < KW; ++kj) bf[kj][i] = bn[kj][i];
+            }
+            buf = next;
+        }
+        if (t == t_hi) break;
+#pragma unroll
+        for (int kj = 0; kj < KW; ++kj)
 #pragma unroll
             for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-                for (int ni = 0; ni < 2; ++ni) acc[kj][mi][ni] = mfma<BF16>(af[mi], bf[kj][ni], acc[kj][mi][ni]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (bias) {
+                for (int ni = 0; ni < 2; ++ni) {
+                    tot[kj][mi][ni] = folded ? tot[kj][mi][ni] + acc[kj][mi][ni] : acc[kj][mi][ni];
+                    acc[kj][mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        folded = true;
+    }
+    if (folded) {
 #pragma unroll
-            for (int mi = 0; mi < 2; ++mi) accb[mi] = mfma<BF16>(af[mi], ones, accb[mi]);
-        }
-        issue(buf);
+        for (int kj = 0; kj < KW; ++kj)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            af[i] = an[i];
+            for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-            for (int kj = 0; kj < KW; ++kj) bf[kj][i] = bn[kj][i];
-        }
-        buf = next;
+                for (int ni = 0; ni < 2; ++ni) acc[kj][mi][ni] = tot[kj][mi][ni] + acc[kj][mi][ni];
     }
     // every request must be done before LDS is used for the exchange (and given back)
     arrived(std::integral_constant<int, 0>{});
@@ -559,7 +628,6 @@ __global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *
     // (first half of the pixels + second half, per element).
     // acc[kj][mi][ni][i]: co = wm*32 + mi*16 + (lane>>4)*4 + i, ci = wn*32 + ni*16 + (lane&15)
     float *out = (float *)smem;
-    float *sum = out + KW * 64 * 64;                     // [group][64]
     const int oo = (wm * 32 + (lane >> 4) * 4) * 64 + wn * 32 + (lane & 15);
     if (grp == 1) {
 #pragma unroll
@@ -570,12 +638,6 @@ __global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *
                 for (int ni = 0; ni < 2; ++ni)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) out[oo + (kj * 64 + mi * 16 + i) * 64 + ni * 16] = acc[kj][mi][ni][i];
-    }
-    if (bias && (lane & 15) == 0) {                      // every column holds the sum
-#pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) sum[grp * 64 + wm * 32 + mi * 16 + (lane >> 4) * 4 + i] = accb[mi][i];
     }
     __syncthreads();
     if (grp == 0) {
@@ -604,7 +666,6 @@ __global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *
         __builtin_amdgcn_raw_ptr_buffer_atomic_fadd_f32(out[row * 64 + lane], rw, lo,
                                                         (row & 63) * rowb + (row >> 6) * G.cin * 4, 0);
     }
-    if (has_db && wave == 0) unsafeAtomicAdd(&db[co0 + lane], sum[lane] + sum[64 + lane]);
 }
 
 template <bool BF16, int KW, int S>
@@ -804,18 +865,35 @@ hipError_t launch_conv_weight_grad(const uint16_t *x, const uint16_t *g, float *
         R.tw = fwd.wout / 8;
         R.tpi = (fwd.hout / 8) * R.tw;
         R.tiles = fwd.n * R.tpi;
+        R.npix = fwd.n * fwd.hout * fwd.wout;
         R.ci_tiles = (fwd.cin + 63) / 64;
         const int base = (fwd.cout / 64) * R.ci_tiles * fwd.kh;
-        // About 128 workgroups: fewer leave CUs idle, more add to the same addresses more
-        // often (64 -> 64, 3x3, 128 x 256 pixels: 21.0 us with 63 workgroups, 16.6 with 126,
-        // 18.3 with 255).
-        int splits = base >= 128 ? 1 : 128 / base;
-        if (splits > R.tiles) splits = R.tiles;
+        // Splits of the tiles. More splits shorten a workgroup's run (a tile's time is that of
+        // its loads, 2 to 4 KB per wave) and add to dW more often. Over 60 shapes the time is
+        // least near sqrt(6 KB * tiles / base), and up to 48 workgroups cost nothing. Not more
+        // workgroups, db's among them, than run at once (a second round: 3x3 256 -> 256 at
+        // 128 x 256, 79 us with 5 splits, 118 with 6; CUs with two of them and CUs with one,
+        // which 1x1 layers' LDS allows: 256 -> 256 at 256 x 256, 44 us with 400, 29 with 512),
+        // nor more additions per address than 16 + one per 2048 pixels: each rounds the whole
+        // sum (1x1 64 -> 64 at 64 x 128, values of one sign: error 7.2e-8 with the general
+        // form, 6.4e-8 with 20 additions, 8.1e-8 with 32, 1.5e-7 with 128).
+        const int kb = fwd.kh == 1 ? 2 : 2 + fwd.stride;
+        const float best = sqrtf(6.f * kb * R.tiles / base);
+        const int slots = fwd.kh == 1 && best * base >= 512.f ? 512 : 256;
+        const int cot = fwd.cout / 64;
+        const int fit = (int)((slots / cot - 1) / (R.ci_tiles * fwd.kh + 0.5f));
+        int splits = std::max((int)(best + 0.5f), 48 / base);
+        splits = std::min({splits, fit, R.tiles, 16 + R.npix / 2048});
+        if (splits < 1) splits = 1;
         R.run = (R.tiles + splits - 1) / splits;
         R.splits = (R.tiles + R.run - 1) / R.run;
         R.x_bytes = (int)((size_t)fwd.n * fwd.hin * fwd.win * fwd.cin * 2);
         R.g_bytes = (int)((size_t)fwd.n * fwd.hout * fwd.wout * fwd.cout * 2);
-        const unsigned grid = (unsigned)(base * R.splits);
+        R.wgs = base * R.splits;
+        // db: about twice the pixels of a run per workgroup, less than its time
+        R.bias_px = kBiasPx * ((R.run + 7) / 8);
+        R.bias_runs = (R.npix + R.bias_px - 1) / R.bias_px;
+        const unsigned grid = (unsigned)(R.wgs + (db ? (fwd.cout / 64) * R.bias_runs : 0));
         auto go = [&](auto kw, auto st) {
             constexpr int KW = decltype(kw)::value, S = decltype(st)::value;
             return bf16 ? launch_wgrad_row<true, KW, S>(x, g, dw, db, R, grid, s)

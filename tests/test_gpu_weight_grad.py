@@ -23,6 +23,8 @@ CASES = [
     (1, 200, 192, 1, 2, 16, 8, "f16", True),
     (1, 64, 64, 3, 1, 128, 64, "bf16", True),     # several tiles per run, a shorter last run
     (1, 256, 256, 3, 1, 32, 32, "bf16", True),    # as many tiles of (co, ci) as workgroups
+    (1, 512, 256, 3, 1, 48, 56, "f16", True),     # runs of 21 tiles: one batch joined, a shorter one
+    (1, 512, 512, 3, 1, 48, 48, "bf16", True),    # one run of 36 tiles: two batches joined
 ]
 
 
@@ -63,6 +65,32 @@ def test_weight_grad_outside_values_stay_out():
     bc.bc_conv2d_weight_grad((3, 3, 1, 1, 0), x, g, dw, None)
     bad = ~torch.isfinite(dw)
     assert bool(bad[:, :, 1:, 5].all()) and int(bad.sum()) == 64 * 3 * 2
+
+
+@pytest.mark.parametrize("cin,cout,k", [(256, 256, 3), (64, 64, 1)])
+def test_weight_grad_no_less_accurate_than_the_general_form(cin, cout, k):
+    """Long sums of values of one sign, where every rounding counts: the gradients of a map
+    of whole 8 x 8 tiles (64 x 128) are at most as far from 64 bits as those of a map of
+    about as many pixels that the general form takes (64 x 124; 3 % fewer terms, 5 % for
+    the spread between inputs)."""
+    from paper_2108_09376_amd import bc
+    g = torch.Generator(device="cuda").manual_seed(11)
+    err = {}
+    for w in (128, 124):
+        x = torch.randn((1, 64, w, cin), generator=g, device="cuda").relu().bfloat16()
+        go = (torch.randn((1, 64, w, cout), generator=g, device="cuda").abs() * 0.1).bfloat16()
+        dw = torch.zeros((cout, k, k, cin), device="cuda")
+        db = torch.zeros(cout, device="cuda")
+        bc.bc_conv2d_weight_grad((k, k, 1, k // 2, 0), x, go, dw, db)
+        xp = torch.nn.functional.pad(x.double(), (0, 0, k // 2, k // 2, k // 2, k // 2))
+        gd = go.double().reshape(-1, cout).t().contiguous()
+        want = torch.stack([gd @ xp[:, i:i + 64, j:j + w].reshape(-1, cin) for i in range(k) for j in range(k)], 1)
+        rel = lambda a, b: float((a.double() - b).norm() / b.norm())
+        err[w] = rel(dw.reshape(want.shape), want), rel(db, gd.sum(1))
+    print(err)
+    assert err[128][0] <= 1.08 * err[124][0]
+    # 64 or 256 sums only: their spread between inputs is about 1 / sqrt(2 * 64) each side
+    assert err[128][1] <= 1.3 * err[124][1]
 
 
 @pytest.mark.parametrize("counts", [(1, 255, 1024, 1025), (4096, 2049, 3)])
