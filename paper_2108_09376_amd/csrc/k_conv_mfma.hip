@@ -1517,8 +1517,9 @@ bool make_plan(const LayerGeom &g, int BM, int BN, Plan &pl)
 // active block, 9.1 -> 8.4 us with 38; frames -0.7 % at 30 %, +1.5 % with every block).
 // Other forms take the largest tile with >= 2048 workgroups on a full frame. The choice
 // depends on the layer's shape only, never on the active count, so an active block's
-// result does not depend on which other blocks are active.
-bool choose_plan(const LayerGeom &g, Plan &best)
+// result does not depend on which other blocks are active. `dma`: x and w are aligned to
+// 16 bytes, which the wave-K form's requests to LDS need.
+bool choose_plan(const LayerGeom &g, Plan &best, bool dma = true)
 {
     if ((g.kh == 1 || g.kh == 3) && g.cin % 8 == 0) {
         const int bpx = g.bh * g.bw;
@@ -1571,7 +1572,7 @@ bool choose_plan(const LayerGeom &g, Plan &best)
             // 512->512 at stride 16 25 -> 32 us. A call without an index runs every tile: if
             // its slices are more workgroups than CUs, each tile's workgroup runs them in
             // turn (same sums, same order; 512->512 at stride 32, every block, 22.4 -> 16.2).
-            if (g.kh == 3 && g.stride == 1 && best.BM == 64 && best.BN == 64 && a.nslot <= 192 &&
+            if (dma && g.kh == 3 && g.stride == 1 && best.BM == 64 && best.BN == 64 && a.nslot <= 192 &&
                 ((nchunk >= 8 && tiles > 256 && tiles <= 512) || (nchunk >= 16 && tiles <= 2048))) {
                 // ws_bytes stays: which layers need the workspace, and are refused without it,
                 // is documented by shape and does not change with the form
@@ -1833,7 +1834,7 @@ namespace {
 void fill_plan(const uint16_t *x, const uint16_t *w, const float *bias, const uint16_t *res,
                uint16_t *y, int relu, const LayerGeom &g, Plan &p)
 {
-    choose_plan(g, p);
+    choose_plan(g, p, (((uintptr_t)x | (uintptr_t)w) & 15) == 0);
     MfmaArgs &a = p.a;
     a.x = x; a.w = w; a.bias = bias; a.res = res; a.y = y;
     a.idx = g.idx; a.count = g.count;

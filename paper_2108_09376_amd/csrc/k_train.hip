@@ -856,8 +856,9 @@ hipError_t launch_conv_weight_grad(const uint16_t *x, const uint16_t *g, float *
     // before -> with it: 3x3 64 -> 64 at 128 x 256 23.2 -> 16.6, 128 -> 128 at 64 x 128 19.6
     // -> 16.0, 32 -> 64 stride 2 20.7 -> 15.6; 1x1 64 -> 128 13.9 -> 7.0), not for 3x3 layers
     // below 1024 output pixels (8 x 16 pixels 4.8 -> 6.1), nor where the uniform offsets of
-    // a 64-row tile could pass 2 GiB.
-    if (fwd.hout % 8 == 0 && fwd.wout % 8 == 0 && fwd.cin <= (1 << 18) &&
+    // a 64-row tile could pass 2 GiB, nor for maps not aligned to 16 bytes, which the
+    // requests to LDS need.
+    if ((((uintptr_t)x | (uintptr_t)g) & 15) == 0 && fwd.hout % 8 == 0 && fwd.wout % 8 == 0 && fwd.cin <= (1 << 18) &&
         (fwd.kh == 1 || fwd.n * fwd.hout * fwd.wout >= 1024)) {
         WgradRow R;
         R.hin = fwd.hin; R.win = fwd.win; R.cin = fwd.cin;

@@ -42,6 +42,13 @@ def weights_dev(w_bits_oihw, dtype, nhwc=True, device="cuda"):
     return t.to(device)
 
 
+def shifted(t, elems):
+    """The same values and shape, contiguous, starting `elems` elements into a buffer."""
+    buf = torch.empty(t.numel() + elems, dtype=t.dtype, device=t.device)
+    v = buf[elems:].view(t.shape)
+    return v.copy_(t)
+
+
 def max_abs_rel(got, want):
     """max |y - y_ref| / max(1, |y_ref|) (the stated tolerance metric)."""
     got = np.asarray(got, np.float64)

@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 import synth
-from _util import block_select, from_dev, to_dev, weights_dev
+from _util import block_select, from_dev, shifted, to_dev, weights_dev
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -95,3 +95,19 @@ def test_wave_k_bits_do_not_depend_on_the_call(B, shape):
         sel = block_select(mask, got.shape)
         assert np.array_equal(got[sel], full[sel]), frac
         assert not got[~sel].any()
+
+
+@pytest.mark.parametrize("which", ["x", "w"])
+def test_wave_k_shapes_take_any_alignment(B, which):
+    """A map or weights that start 8 bytes off a 16-byte boundary (a view into a buffer) give
+    the exact result too: the form whose loads need the alignment is not taken."""
+    r = synth.rng(7150)
+    x = to_dev(synth.to_storage_bits(synth.small_ints(r, (1, 512, 24, 32), -2, 2), "bf16"), "bf16")
+    wt = weights_dev(synth.to_storage_bits(synth.small_ints(r, (128, 512, 3, 3), -1, 1), "bf16"), "bf16")
+    outs = []
+    for off in (0, 4):
+        out = torch.zeros((1, 24, 32, 128), dtype=torch.bfloat16, device="cuda")
+        xs, ws = (shifted(x, off), wt) if which == "x" else (x, shifted(wt, off))
+        B.bc_sparse_conv2d((3, 3, 1, 1, 0), xs, B.BC_NHWC, ws, None, None, out, (3, 4), None, None)
+        outs.append(out)
+    assert outs[0].float().abs().sum() > 0 and torch.equal(outs[0], outs[1])

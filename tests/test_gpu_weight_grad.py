@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import synth
-from _util import to_dev
+from _util import shifted, to_dev
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -65,6 +65,23 @@ def test_weight_grad_outside_values_stay_out():
     bc.bc_conv2d_weight_grad((3, 3, 1, 1, 0), x, g, dw, None)
     bad = ~torch.isfinite(dw)
     assert bool(bad[:, :, 1:, 5].all()) and int(bad.sum()) == 64 * 3 * 2
+
+
+@pytest.mark.parametrize("which", ["x", "g"])
+def test_weight_grad_takes_any_alignment(which):
+    """Maps that start 8 bytes off a 16-byte boundary give the exact result too (small
+    integers): the form whose loads need the alignment is not taken."""
+    from paper_2108_09376_amd import bc
+    r = synth.rng(7650)
+    x = to_dev(synth.to_storage_bits(synth.small_ints(r, (1, 64, 32, 40), -2, 2), "bf16"), "bf16")
+    g = to_dev(synth.to_storage_bits(synth.small_ints(r, (1, 64, 32, 40), -2, 2), "bf16"), "bf16")
+    res = []
+    for off in (0, 4):
+        dw, db = torch.zeros((64, 3, 3, 64), device="cuda"), torch.zeros(64, device="cuda")
+        xs, gs = (shifted(x, off), g) if which == "x" else (x, shifted(g, off))
+        bc.bc_conv2d_weight_grad((3, 3, 1, 1, 0), xs, gs, dw, db)
+        res.append((dw, db))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
 
 
 @pytest.mark.parametrize("cin,cout,k", [(256, 256, 3), (64, 64, 1)])
