@@ -97,7 +97,8 @@ struct MfmaArgs {
     FastDiv f_hrhc, f_hc, f_rbw, f_bw;  // divisions by HR*HC, HC, R*bw, bw
     int ksplit, cps;                    // K slices per tile, 32-channel chunks per slice
     int kseq;                           // wave-K form: slices one workgroup runs in order
-    int perm8;                          // wave-K form: rows permuted for 8-pixel-wide blocks
+    int perm8;                          // wave-K form: rows permuted for 8-pixel-wide tiles
+    int tw, tpr;                        // wave-K form: tile width, tiles per row of the block
     int tiles_full;                     // tiles (incl. K slices) of a full frame
     int slots;                          // stem form: workgroups resident on the device
     int xu, gx;                         // XCD grouping of the tile order (xcd_tile), 0 = off
@@ -161,15 +162,24 @@ struct TileBlocks {
     int live;
 };
 
+// CUT: a block's tiles are R rows of a.tw columns, a.tpr side by side (else all its columns).
+template <bool CUT = false>
 __device__ __forceinline__ bool load_tile_blocks(const MfmaArgs &a, int mt, TileBlocks &tb)
 {
     const int tid = threadIdx.x;
     if (tid < a.P) {
         const int cnt = a.count ? *a.count : a.total_blocks;
-        int k, r0;
+        int k, r0, q0 = 0;
         if (a.P == 1) {
             k = mt / a.tpb;
-            r0 = (mt - k * a.tpb) * a.R;
+            const int t = mt - k * a.tpb;
+            r0 = t * a.R;
+            if constexpr (CUT)
+                if (a.tpr > 1) {
+                    const int row = t / a.tpr;
+                    r0 = row * a.R;
+                    q0 = (t - row * a.tpr) * a.tw;
+                }
         } else {
             k = mt * a.P + tid;
             r0 = 0;
@@ -182,7 +192,7 @@ __device__ __forceinline__ bool load_tile_blocks(const MfmaArgs &a, int mt, Tile
                 const int rem = bid - img * a.gh * a.gw;
                 const int gy = rem / a.gw;
                 oy0 = gy * a.bh + r0;
-                ox0 = (rem - gy * a.gw) * a.bw;
+                ox0 = (rem - gy * a.gw) * a.bw + q0;
             }
         }
         tb.img[tid] = img;
@@ -201,8 +211,8 @@ __device__ __forceinline__ bool load_tile_blocks(const MfmaArgs &a, int mt, Tile
 // the storage format and writes with 16-byte buffer stores; rows of inactive patches
 // use an out-of-range offset, which the hardware drops. `tid` is the thread's index in
 // its group of four waves; a group that is not `live` only takes the barriers.
-// PERM: the rows of a 64-row tile of one 8-pixel-wide block may be permuted (a.perm8): row
-// 16 mi + 8 h + c of the tile is pixel row mi + 4 h, column c of the block.
+// PERM: a tile of one block is a.tw pixels wide, and its 64 rows may be permuted if that is
+// eight (a.perm8): row 16 mi + 8 h + c of the tile is pixel row mi + 4 h, column c.
 __device__ __forceinline__ int perm8_row(int m) { return (((m >> 4) + 4 * ((m >> 3) & 1)) << 3) + (m & 7); }
 
 template <bool BF16, int BM, int BN, bool PERM = false>
@@ -227,14 +237,14 @@ struct Epilogue {
             bias[np][0] = bload(br, co * 4);
             bias[np][1] = bload(br, co * 4 + 16);
         }
-        const int rbw = a.R * a.bw;
+        const int bw = PERM ? a.tw : a.bw, rbw = a.R * bw;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             int m = wm * WM + (lane >> 2) + 16 * u;
             if constexpr (PERM) m = a.perm8 ? perm8_row(m) : m;
             const int p = fdiv(m, a.f_rbw);
             const int local = m - p * rbw;
-            const int pr = fdiv(local, a.f_bw), pc = local - pr * a.bw;
+            const int pr = fdiv(local, a.f_bw), pc = local - pr * bw;
             const int img = tb.img[p];
             rowoff[u] = img >= 0 ? (((img * a.hout + tb.oy0[p] + pr) * a.wout + tb.ox0[p] + pc) *
                                     a.cout) * 2
@@ -884,7 +894,7 @@ __global__ __launch_bounds__(kThreads) void k_conv_pipe_pair(MfmaArgs a1, MfmaAr
 //    q ^ ((row >> 1) & 3): the loads write 1 KB linearly, so the swizzle is in which
 //    quarter a lane requests, and sixteen consecutive rows read at one quarter use all 64
 //    banks (no conflicts counted; >> 2 in its place: 3.6 of 7.3 cycles per read). Of an
-//    8-pixel-wide block a fragment takes pixel rows r and r + 4 (perm8): with halo rows of
+//    8-pixel-wide tile a fragment takes pixel rows r and r + 4 (perm8): with halo rows of
 //    10 slots these are 40 slots apart, which is conflict free too, and adjacent rows, 10
 //    slots apart, are not (3.6 of 7.3 cycles).
 // The four partial tiles are added through LDS in wave order, wave w finishing quadrant w.
@@ -968,7 +978,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv_wavek3(MfmaArgs a)
     const int ks = L % a.ksplit, mn = L / a.ksplit;
     const int nt = mn % a.ntn, mt = mn / a.ntn;
     const int n0 = nt * 64;
-    if (!load_tile_blocks(a, mt, tb)) return;   // tile beyond the active count (uniform)
+    if (!load_tile_blocks<true>(a, mt, tb)) return;   // tile beyond the active count (uniform)
     Epilogue<BF16, 64, 64, true> epi;
     epi.prefetch(a, tb, n0);
     const int lane = threadIdx.x & 63;
@@ -1009,14 +1019,14 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv_wavek3(MfmaArgs a)
         dma16(wd, lring + slot * 4096 + v * 1024, c * BK + q * 8 < a.cin ? off : kOutOfRange);
     };
     int sl[4];                                           // halo slot of this lane's rows at tap (0, 0)
-    const int rbw = a.R * a.bw;
+    const int rbw = a.R * a.tw;
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi) {
         const int r = mi * 16 + (lane & 15);
         const int m = a.perm8 ? perm8_row(r) : r;
         const int p = fdiv(m, a.f_rbw);
         const int local = m - p * rbw;
-        const int pr = fdiv(local, a.f_bw), pc = local - pr * a.bw;
+        const int pr = fdiv(local, a.f_bw), pc = local - pr * a.tw;
         sl[mi] = p * hrhc + pr * a.HC + pc;
     }
     const int bo = (lane & 15) * 64 + (((lane >> 4) ^ ((lane >> 1) & 3)) << 4);
@@ -1448,6 +1458,8 @@ bool make_plan(const LayerGeom &g, int BM, int BN, Plan &pl)
     a.ksplit = 1;
     a.kseq = 1;
     a.perm8 = 0;
+    a.tw = g.bw;
+    a.tpr = 1;
     a.cps = (g.cin + BK - 1) / BK;
     pl.ws_bytes = 0;
     if (g.cin % 8) {
@@ -1574,6 +1586,21 @@ bool choose_plan(const LayerGeom &g, Plan &best, bool dma = true)
             // turn (same sums, same order; 512->512 at stride 32, every block, 22.4 -> 16.2).
             if (dma && g.kh == 3 && g.stride == 1 && best.BM == 64 && best.BN == 64 && a.nslot <= 192 &&
                 ((nchunk >= 8 && tiles > 256 && tiles <= 512) || (nchunk >= 16 && tiles <= 2048))) {
+                // The bands of 32-wide blocks are cut into 8x8 or 4x16 pixels, their halo being
+                // above 7 KB: requests fill LDS no faster than the products use it (256 -> 128, 4x32
+                // blocks, no index: 20.0 us in the pipelined form, 21.3 with 2x32 bands, 19.2
+                // cut).
+                if (a.P == 1 && a.nslot > 112)
+                    for (int e = 8; e <= 16; e *= 2)
+                        if (g.bw > e && g.bw % e == 0 && g.bh % (64 / e) == 0) {
+                            a.R = 64 / e;
+                            a.tw = e;
+                            a.tpr = g.bw / e;
+                            a.HR = a.R + 2;
+                            a.HC = e + 2;
+                            a.nslot = a.HR * a.HC;
+                            break;
+                        }
                 // ws_bytes stays: which layers need the workspace, and are refused without it,
                 // is documented by shape and does not change with the form
                 if (tiles > 256) {
@@ -1587,7 +1614,7 @@ bool choose_plan(const LayerGeom &g, Plan &best, bool dma = true)
                     best.grid = tiles;
                 }
                 best.wavek = a.nslot <= 112 ? 7 : a.nslot <= 144 ? 9 : 12;
-                a.perm8 = a.P == 1 && g.bw == 8 && a.R == 8;
+                a.perm8 = a.P == 1 && a.tw == 8 && a.R == 8;
                 best.lds = 4 * (size_t)wavek3_bytes(best.wavek, wavek3_depth(best.wavek));
             }
             // 1x1 layers with 64x64 tiles stage two chunks per barrier (a same-process A/B
@@ -1853,8 +1880,8 @@ void fill_plan(const uint16_t *x, const uint16_t *w, const float *bias, const ui
         a.f_hrhc = make_fastdiv(a.HR * a.HC > 0 ? a.HR * a.HC : 1);
         a.f_hc = make_fastdiv(a.HC > 0 ? a.HC : 1);
     }
-    a.f_rbw = make_fastdiv(a.R * g.bw);
-    a.f_bw = make_fastdiv(g.bw);
+    a.f_rbw = make_fastdiv(a.R * a.tw);
+    a.f_bw = make_fastdiv(a.tw);
 }
 
 // Where a split plan keeps its partials: the library-owned workspace, or the fixed

@@ -29,8 +29,10 @@ CASES = [
     (1, 256, 320, 6, 9, 8, 8, "bf16", True, 0.3),     # 270 tiles, K whole, two chunks per wave
     (1, 232, 320, 6, 9, 8, 8, "f16", False, 0.3),     # eight chunks, the last of 8 channels
     (1, 512, 64, 2, 2, 16, 16, "bf16", False, 0.5),   # bands of a 16-wide block
-    (1, 512, 64, 1, 2, 32, 32, "f16", False, 1.0),    # bands of a 32-wide block
-    (1, 512, 64, 1, 1, 4, 64, "bf16", True, 1.0),     # one block, one-row bands
+    (1, 512, 64, 1, 2, 32, 32, "f16", False, 1.0),    # a 32-wide block cut into 8x8 tiles
+    (1, 512, 64, 2, 2, 12, 32, "bf16", True, 0.6),    # cut into 4x16 tiles
+    (1, 512, 64, 2, 2, 2, 32, "f16", False, 0.6),     # two rows: not cut, a 136-slot halo
+    (1, 512, 64, 1, 1, 4, 64, "bf16", True, 1.0),     # 64 wide: the halo is too large, another form
     (1, 512, 64, 4, 4, 2, 4, "bf16", False, 0.4),     # eight 2x4 patches: the largest halo
     (1, 512, 64, 3, 5, 8, 8, "bf16", False, 0.07),    # one active block
     (1, 232, 64, 3, 5, 8, 8, "bf16", False, 0.3),     # few tiles, eight chunks: another form
