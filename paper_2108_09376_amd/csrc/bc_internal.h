@@ -23,6 +23,11 @@ struct LayerGeom {
 // Storage formats of the half-width paths.
 enum class Half16 { BF16, F16 };
 
+// Before a launch with `lds` bytes of dynamic LDS: opts the kernel in to 60 KB or more
+// (gfx950: 160 KB per workgroup, static shared memory included), once per kernel, device
+// and largest size so far.
+hipError_t allow_lds(const void *kernel, size_t lds);
+
 hipError_t launch_block_index(const uint8_t *mask, int total, int32_t *idx, int32_t *count,
                               hipStream_t s);
 

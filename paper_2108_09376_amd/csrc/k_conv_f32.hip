@@ -222,11 +222,8 @@ template <int KS>
 hipError_t launch_ks(const F32Args &a, unsigned grid, size_t lds, hipStream_t s)
 {
     auto kern = k_conv_nchw_f32<KS>;
-    if (lds > 60 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)lds);
-        if (e != hipSuccess) return e;
-    }
+    const hipError_t e = allow_lds((const void *)kern, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, s, a);
     return hipGetLastError();
 }

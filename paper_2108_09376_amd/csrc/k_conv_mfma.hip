@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "bc_internal.h"
+#include "lds_dma.h"
 
 namespace bc {
 namespace {
@@ -45,13 +46,7 @@ typedef short short8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x3 __attribute__((ext_vector_type(3)));
-
-// Raw buffer resource: no swizzle, 32-bit dword data format; loads at offsets beyond
-// num_records return zeros instead of faulting.
-constexpr int kBufferFlags = 0x00020000;
-constexpr int kOutOfRange = 0x7FFFFF00;     // byte offset past every buffer (< 2^31 - 256 bytes)
 
 __device__ __forceinline__ uint4 bload(__amdgpu_buffer_rsrc_t r, int byte_off)
 {
@@ -900,32 +895,12 @@ __global__ __launch_bounds__(kThreads) void k_conv_pipe_pair(MfmaArgs a1, MfmaAr
 // The four partial tiles are added through LDS in wave order, wave w finishing quadrant w.
 // The order of the sums depends on the layer's shape only.
 
-// Raw buffer descriptor as the four dwords that the inline instruction takes.
-__device__ __forceinline__ i32x4 raw_desc(const void *p, int bytes)
-{
-    const uint64_t u = (uint64_t)p;
-    return i32x4{(int)(uint32_t)u, (int)(uint32_t)(u >> 32), bytes, kBufferFlags};
-}
-
-// 64 lanes x 16 bytes from memory to LDS bytes [lds, lds + 1024) (lane i at 16 i). No
-// register receives data; offsets at or beyond the buffer's extent write zeros.
-__device__ __forceinline__ void dma16(const i32x4 &r, uint32_t lds, int voff)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(r) : "memory");
-}
-
 // At most N requests of this wave outstanding, and every LDS read done (the slot the
 // last fragments came from may be overwritten).
 template <int N>
 __device__ __forceinline__ void wait_dma()
 {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory");
-}
-
-__device__ __forceinline__ uint32_t lds_addr(const void *p)
-{
-    return (uint32_t)(uint64_t)(__attribute__((address_space(3))) const uint8_t *)p;
 }
 
 // Adds the four waves' partial tiles (4 x 4 fragments) in wave order; wave w gets quadrant
@@ -1740,6 +1715,7 @@ hipError_t scratch_ptr(float **out)
 // memory either); the library has a few dozen kernel instantiations.
 struct LdsOptIn {
     const void *fn;
+    int dev;
     size_t lds;
 };
 constexpr int kMaxOptIn = 256;
@@ -1747,26 +1723,33 @@ std::mutex g_attr_mu;
 LdsOptIn g_attr_lds[kMaxOptIn];
 int g_attr_n = 0;
 
+}  // namespace
+
+hipError_t allow_lds(const void *kernel, size_t lds)
+{
+    if (lds < 60 * 1024) return hipSuccess;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lk(g_attr_mu);
+    int i = 0;
+    while (i < g_attr_n && (g_attr_lds[i].fn != kernel || g_attr_lds[i].dev != dev)) ++i;
+    if (i < g_attr_n && g_attr_lds[i].lds >= lds) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    if (i == kMaxOptIn) return hipSuccess;               // not remembered: set again by the next launch
+    if (i == g_attr_n) ++g_attr_n;
+    g_attr_lds[i] = LdsOptIn{kernel, dev, lds};
+    return hipSuccess;
+}
+
+namespace {
+
 template <typename K>
 hipError_t launch_kernel(K kernel, const Plan &p, hipStream_t s)
 {
-    if (p.lds >= 60 * 1024) {
-        // opt in to 60 KB or more of dynamic LDS (gfx950: 160 KB per workgroup, static
-        // shared memory included), raised per kernel to the largest size launched so far
-        std::lock_guard<std::mutex> lk(g_attr_mu);
-        int i = 0;
-        while (i < g_attr_n && g_attr_lds[i].fn != (const void *)kernel) ++i;
-        if (i == g_attr_n) {
-            if (g_attr_n == kMaxOptIn) return hipErrorOutOfMemory;
-            g_attr_lds[g_attr_n++] = LdsOptIn{(const void *)kernel, 0};
-        }
-        if (g_attr_lds[i].lds < p.lds) {
-            const hipError_t e = hipFuncSetAttribute(
-                (const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
-            if (e != hipSuccess) return e;
-            g_attr_lds[i].lds = p.lds;
-        }
-    }
+    const hipError_t e = allow_lds((const void *)kernel, p.lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(p.grid), dim3(kThreads * p.wgs), p.lds, s, p.a);
     return hipSuccess;
 }

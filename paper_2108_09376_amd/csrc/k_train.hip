@@ -35,19 +35,17 @@
 #include <type_traits>
 
 #include "bc_internal.h"
+#include "lds_dma.h"
 
 namespace bc {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kBufferFlags = 0x00020000;     // raw buffer, dword format
-constexpr int kOutOfRange = 0x7FFFFF00;      // loads return 0, stores are dropped
 
 typedef short short8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 template <bool BF16>
 __device__ __forceinline__ float h16_to_f32(uint32_t h)
@@ -375,18 +373,6 @@ __global__ __launch_bounds__(kThreads) void k_wgrad16(const uint16_t *__restrict
 //  * the bias gradient has workgroups of its own at the end of the grid (bias_run).
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void dma16(const i32x4 &r, uint32_t lds, int voff)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(r) : "memory");
-}
-
-__device__ __forceinline__ i32x4 raw_desc(const void *p, int bytes)
-{
-    const uint64_t u = (uint64_t)p;
-    return i32x4{(int)(uint32_t)u, (int)(uint32_t)(u >> 32), bytes, kBufferFlags};
-}
-
 // Eight pixels of one channel: two transposed reads of four pixels each.
 __device__ __forceinline__ short8 read_tr(const uint8_t *lo, const uint8_t *hi)
 {
@@ -488,8 +474,7 @@ __global__ __launch_bounds__(kRowThreads, 1) void k_wgrad_row16(const uint16_t *
     const int co0 = cot * 64, ci0 = cit * 64;
     const int t_lo = split * G.run, t_hi = min(G.tiles, t_lo + G.run);
     const i32x4 xd = raw_desc(x, G.x_bytes), gd = raw_desc(g, G.g_bytes);
-    const uint32_t lbase = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uint64_t)(__attribute__((address_space(3))) uint8_t *)smem);
+    const uint32_t lbase = __builtin_amdgcn_readfirstlane(lds_addr(smem));
     // this lane's part of a request of 8 rows: row lane >> 3, 16-byte unit lane & 7 of LDS;
     // f of its row (8 (wave + 8 v) + (lane >> 3)) does not depend on v
     const int row8 = 8 * wave + (lane >> 3);
@@ -674,10 +659,8 @@ hipError_t launch_wgrad_row(const uint16_t *x, const uint16_t *g, float *dw, flo
 {
     constexpr int lds = WgradShape<KW, S>::NB * WgradShape<KW, S>::BUF;
     auto kern = k_wgrad_row16<BF16, KW, S>;
-    if (lds > 60 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-    }
+    const hipError_t e = allow_lds((const void *)kern, lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kRowThreads), lds, s, x, g, dw, db, G);
     return hipGetLastError();
 }
