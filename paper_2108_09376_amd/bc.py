@@ -191,18 +191,23 @@ def _sizes(shape, dtype: int, layout: int) -> bc_tensor:
 _shared_sizes = functools.lru_cache(maxsize=1024)(_sizes)
 
 
-def desc(t, layout: int, _make=_sizes) -> bc_tensor:
-    """bc_tensor of a contiguous 4-D tensor stored NHWC ([N,H,W,C]) or NCHW ([N,C,H,W])."""
+def _check_map(t):
     if not t.is_contiguous():
         raise ValueError("tensors passed to the library must be contiguous")
     if t.dim() != 4:
         raise ValueError("feature maps are 4-D")
-    return _make(t.shape, _dtype_code(t), layout)
+
+
+def desc(t, layout: int) -> bc_tensor:
+    """bc_tensor of a contiguous 4-D tensor stored NHWC ([N,H,W,C]) or NCHW ([N,C,H,W])."""
+    _check_map(t)
+    return _sizes(t.shape, _dtype_code(t), layout)
 
 
 def _desc(t, layout: int) -> bc_tensor:
     """desc with the structure shared between equal arguments, for passing by value only."""
-    return desc(t, layout, _shared_sizes)
+    _check_map(t)
+    return _shared_sizes(t.shape, _dtype_code(t), layout)
 
 
 @functools.lru_cache(maxsize=256)

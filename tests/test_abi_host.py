@@ -48,6 +48,24 @@ def test_library_exports_every_declared_symbol(B):
         assert re.search(rf"\bT {n}$", out, re.M), n
 
 
+def test_descriptors_are_the_callers_own(B):
+    """desc takes a tensor and a layout and gives a structure that the caller may change:
+    what the binding shares between its own calls stays as it was."""
+    import inspect
+    import torch
+    assert list(inspect.signature(B.desc).parameters) == ["t", "layout"]
+    t = torch.zeros((1, 8, 16, 32), dtype=torch.bfloat16)
+    a, shared = B.desc(t, B.BC_NHWC), B._desc(t, B.BC_NHWC)
+    a.c = 5
+    again = B.desc(t, B.BC_NHWC)
+    assert (again.n, again.h, again.w, again.c) == (1, 8, 16, 32)
+    assert B._desc(t, B.BC_NHWC) is shared and shared.c == 32
+    with pytest.raises(ValueError):
+        B.desc(t[0], B.BC_NHWC)
+    with pytest.raises(ValueError):
+        B._desc(t.transpose(1, 2), B.BC_NHWC)
+
+
 def test_status_strings(B):
     for s in range(12):
         assert B.status_name(s) and B.status_name(s) != "unknown status"
