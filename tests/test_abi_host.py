@@ -472,8 +472,11 @@ def test_noalloc_validation_and_scratch_limit(B):
     assert noalloc_call(B, grid=(7, 16))[0] == E.BC_ERR_NOT_DIVISIBLE
     assert noalloc_call(B, d_out=FAKE_IN + 100)[0] == E.BC_ERR_ALIAS
     assert noalloc_call(B, out=(1, 48, 64, 128, 1, 1))[0] == E.BC_ERR_UNSUPPORTED
-    # 3x3 512 -> 1024 on a 64x128 map with 8x8 blocks: 2048 full-frame tiles split in two,
-    # 2048 * 2 * 64 * 64 * 4 bytes = 64 MiB of partials
+    # 3x3 512 -> 1024 at stride 2 onto a 64x128 map with 8x8 blocks: 2048 full-frame tiles
+    # split in two, 2048 * 2 * 64 * 64 * 4 bytes = 64 MiB of partials
+    st, msg = noalloc_call(B, conv=(3, 3, 2, 1, 1), inp=(1, 512, 128, 256, 1, 1), out=(1, 1024, 64, 128, 1, 1))
+    assert st == E.BC_ERR_CAPACITY and "scratch" in msg
+    # at stride 1 the same shape is refused by size too, though it keeps K whole
     st, msg = noalloc_call(B, inp=(1, 512, 64, 128, 1, 1), out=(1, 1024, 64, 128, 1, 1))
     assert st == E.BC_ERR_CAPACITY and "scratch" in msg
     # 3x3 1024 -> 512: 1024 tiles, 32 MiB

@@ -113,26 +113,28 @@ def test_split_workspace_not_allocated_under_capture(R):
 
 
 def test_captured_split_call_survives_larger_eager_calls(R):
-    """A captured split-K call keeps a valid workspace after eager split calls of other,
-    larger layers (the workspace is never freed or moved): its replays equal eager runs."""
+    """A captured split-K call keeps a valid workspace after eager calls of other layers that
+    write partials over all of it (stride 2), or that need it by shape but keep K whole
+    (stride 1); the workspace is never freed or moved: its replays equal eager runs."""
     from paper_2108_09376_amd import bc
 
     def dev(bits):
         return torch.from_numpy(bits.view(np.int16)).view(torch.bfloat16).cuda()
 
-    def layer(seed, cin, cout, h, w, k):
+    def layer(seed, cin, cout, h, w, k, s=1):
         r = synth.rng(seed)
         x = dev(synth.to_storage_bits(synth.normal(r, (1, h, w, cin)), "bf16"))
         wt = dev(synth.to_storage_bits(synth.he_normal(r, cout, cin, k, k).transpose(0, 2, 3, 1).copy(), "bf16"))
         b = torch.from_numpy(synth.normal(r, cout, 0.1)).cuda()
-        return ((k, k, 1, k // 2, 1), x, bc.BC_NHWC, wt, b, None)
+        return ((k, k, s, k // 2, 1), x, bc.BC_NHWC, wt, b, None)
 
     idx = torch.arange(128, dtype=torch.int32, device="cuda")
     cnt = torch.full((1,), 128, dtype=torch.int32, device="cuda")
     idx_s = torch.arange(32, dtype=torch.int32, device="cuda")
     cnt_s = torch.full((1,), 32, dtype=torch.int32, device="cuda")
     small = layer(980, 512, 512, 16, 32, 3)          # 4x8 grid below: 64 tiles, 4 slices
-    big = layer(981, 1024, 1024, 64, 128, 3)         # 2048 tiles, 2 slices: 64 MiB of partials
+    big = layer(981, 1024, 1024, 64, 128, 3)         # 2048 tiles, K whole
+    big2 = layer(982, 512, 1024, 128, 256, 3, 2)     # 2048 tiles, 2 slices: 64 MiB of partials
     out = torch.zeros((1, 16, 32, 512), dtype=torch.bfloat16, device="cuda")
     bc.bc_sparse_conv2d(*small, out, (4, 8), idx_s, cnt_s)
     torch.cuda.synchronize()
@@ -143,7 +145,8 @@ def test_captured_split_call_survives_larger_eager_calls(R):
     bc.bc_sparse_conv2d(*small, ref, (4, 8), idx_s, cnt_s)
     big_out = torch.zeros((1, 64, 128, 1024), dtype=torch.bfloat16, device="cuda")
     for rep in range(2):
-        bc.bc_sparse_conv2d(*big, big_out, (8, 16), idx, cnt)    # eager, largest partials
+        bc.bc_sparse_conv2d(*big, big_out, (8, 16), idx, cnt)
+        bc.bc_sparse_conv2d(*big2, big_out, (8, 16), idx, cnt)   # eager, largest partials
         torch.cuda.synchronize()
         out.zero_()
         torch.cuda.synchronize()

@@ -1,7 +1,8 @@
 """The wave-K convolution form (3x3, stride 1, four waves splitting K) at the sizes where
 it can go wrong: ragged channel counts, waves with unequal or no work, one and several
 patches per tile, every LDS halo size, batches, single blocks, K slices by several
-workgroups and by one in turn. Operands are small integers, so every sum is exact in fp32
+workgroups and by one in turn, K whole on few and many tiles; and some shapes just outside,
+which other forms compute. Operands are small integers, so every sum is exact in fp32
 and the comparison is byte for byte whatever the order of the sums."""
 import numpy as np
 import pytest
@@ -36,6 +37,9 @@ CASES = [
     (1, 512, 64, 4, 4, 2, 4, "bf16", False, 0.4),     # eight 2x4 patches: the largest halo
     (1, 512, 64, 3, 5, 8, 8, "bf16", False, 0.07),    # one active block
     (1, 232, 64, 3, 5, 8, 8, "bf16", False, 0.3),     # few tiles, eight chunks: another form
+    (1, 520, 192, 6, 8, 8, 8, "f16", True, 0.3),      # 144 tiles: 288 slices by workgroups of their
+                                                      # own, in turn without an index, the last shorter
+    (1, 520, 640, 6, 9, 8, 8, "bf16", True, 0.3),     # 540 tiles, K whole
 ]
 
 

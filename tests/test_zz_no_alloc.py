@@ -2,8 +2,8 @@
 (split-K partials in the library's fixed scratch array), against bc_sparse_conv2d on
 the same inputs: bit for bit on two calls in a row, the second with a smaller input,
 both held to the oracle on sampled active outputs, copied blocks untouched; captured in
-a HIP graph and replayed with new inputs; a layer whose partials exceed the array is
-refused before anything is enqueued."""
+a HIP graph and replayed with new inputs; a layer whose partials exceed the array (or that
+is counted among those by its sizes) is refused before anything is enqueued."""
 import numpy as np
 import pytest
 import torch
@@ -114,8 +114,10 @@ def test_noalloc_graph_replays(B):
         _oracle_check(d, from_dev(out))
 
 
-def test_noalloc_refuses_partials_beyond_scratch(B):
-    d = _draw((512, 1024, 64, 128, 8, 16, 3, 1, 0.3), 960)
+@pytest.mark.parametrize("shape", [(512, 1024, 128, 256, 8, 16, 3, 2, 0.3),    # 64 MiB of partials
+                                   (512, 1024, 64, 128, 8, 16, 3, 1, 0.3)])    # refused by its sizes
+def test_noalloc_refuses_partials_beyond_scratch(B, shape):
+    d = _draw(shape, 960)
     t = _dev(B, d)
     out = to_dev(d["prev"], "bf16")
     torch.cuda.synchronize()
