@@ -168,8 +168,10 @@ bc_status bc_scatter_blocks(const void *d_packed, const int32_t *d_idx, const in
  *  - per-tile arrival counters in a static device array; the last K slice of a tile
  *    resets its counter, so no clearing is needed between calls or graph replays.
  * Both are shared by every call on a device: calls on one device must not overlap
- * in time (use one stream, or order the streams with events). Calls that do not
- * split K use neither. Results never depend on the plan's split: slices are added in
+ * in time (use one stream, or order the streams with events). Other layers use
+ * neither. 3x3 stride-1 layers with 512 or more input channels and 513..2048 full-frame
+ * tiles of 64x64 keep K whole, but are counted among those that split it: they take
+ * part in the workspace's allocation and its refusal, as they always have. Results never depend on the plan's split: slices are added in
  * a fixed order, so an active block's output bits do not depend on the other blocks.
  * Errors: BC_ERR_NULL, BC_ERR_SHAPE, BC_ERR_DTYPE, BC_ERR_LAYOUT,
  * BC_ERR_NOT_DIVISIBLE, BC_ERR_CAPACITY, BC_ERR_ALIAS, BC_ERR_UNINITIALIZED,
@@ -193,8 +195,9 @@ bc_status bc_sparse_conv2d(const bc_conv *conv,
  * The array holds the partials of any layer whose plan needs at most 16 MiB: every
  * layer of ResNet-18/50 and SwiftNet at 2048x1024 with 128-pixel blocks. Layers whose
  * partials need more (3x3 layers with 512 or more input channels and 513..2048 full-
- * frame tiles of 64x64, e.g. 3x3 512->1024 on a 64x128 map with 8x8 blocks) are
- * refused with BC_ERR_CAPACITY before anything is enqueued.
+ * frame tiles of 64x64, e.g. 3x3 512->1024 onto a 64x128 map with 8x8 blocks) are
+ * refused with BC_ERR_CAPACITY before anything is enqueued; at stride 1, where such
+ * layers keep K whole, by the same sizes.
  * The array and the split counters are shared by every call on a device and keep the
  * last call's contents: calls on one device that overlap in time race (use one
  * stream, or order streams with events). Nothing needs clearing between calls.

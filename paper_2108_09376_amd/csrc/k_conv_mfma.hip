@@ -937,7 +937,8 @@ __device__ __forceinline__ void join_waves(f32x4 (&acc)[4][4], f32x4 (&out)[2][2
 }
 
 // LDS bytes of one wave: two halo chunks of HA KB and D weight slices of 4 KB, D as many
-// as 160 KB for four waves allow (5 taps of 64x64 products, about 0.9 us, cover a miss).
+// as 160 KB for four waves allow (5 taps of 64x64 products, about 0.9 us, cover a miss; the
+// 12 KB halos of 2x4-pixel blocks leave room for 3).
 constexpr int wavek3_bytes(int HA, int D) { return 2 * HA * 1024 + D * 4096; }
 constexpr int wavek3_depth(int HA) { return HA <= 7 ? 6 : HA <= 9 ? 5 : 3; }
 
@@ -1493,8 +1494,9 @@ bool make_plan(const LayerGeom &g, int BM, int BN, Plan &pl)
 // fewer output channels the halved tile count costs more: a same-process A/B of whole
 // ResNet-50 frames, 0.6446 -> 0.6330 ms at 30 % active, 0.4699 -> 0.4602 at 10 %);
 // splitting K in two pays off when a full frame has at most 256 tiles (the stride-32
-// layers) and for 3x3 layers with 512 or more input channels and 513 to 2048 tiles
-// (where nine-tap stages do not apply); 1x1 layers with at most 256 tiles split K in
+// layers) and for stride-2 3x3 layers with 512 or more input channels and 513 to 2048 tiles
+// (where nine-tap stages do not apply; at stride 1 the wave-K form, which splits K within
+// the workgroup, is faster, see below); 1x1 layers with at most 256 tiles split K in
 // three from 32 chunks on (ResNet-50's stride-32 2048->512: 0.6410 -> 0.6384 ms at 30 %,
 // no cost at 50 or 100 %) and not below (SwiftNet's decoder laterals with 8 and 16
 // chunks: 7.3 -> 5.3 and 7.2 -> 6.6 us unsplit); three slices of the nine-tap 3x3
@@ -1547,14 +1549,17 @@ bool choose_plan(const LayerGeom &g, Plan &best, bool dma = true)
             }
             // Wave-K form (k_conv_wavek3): stride-1 3x3 layers with 8 chunks on 257 to 512
             // tiles, or 16 chunks on at most 2048 (measured, us per launch, before -> with
-            // it, at 38 of 128 blocks / every block: 256->256 at stride 16 12.5 -> 9.6 / 24.2
-            // -> 18.3; 512->512 at stride 32 14.9 -> 12.0 / 28.2 -> 16.2, at stride 16 30.4 ->
-            // 25.0 / 70.4 -> 51.7). Not for many short tiles (128->128 on 1024 tiles 11.9 ->
-            // 14.6, 256->256 on 2048 26.4 -> 27.3): one 150 KB workgroup per CU overlaps no
-            // tile's start and end. Shorter K on fewer tiles keeps its order of sums: there
-            // the form saves 1 us (128->128 on 256 tiles 8.9 -> 8.0), and the policy network,
-            // whose layers these are and whose update feeds rounding back into its weights,
-            // keeps its bits.
+            // it, at 38 of 128 blocks / every block: 256->256 at stride 16 12.5 -> 9.3 / 24.2
+            // -> 18.6; 512->512 at stride 32 14.9 -> 11.7 / 28.2 -> 16.2, at stride 16 30.4 ->
+            // 25.2 / 70.4 -> 54.9; halos of 12 KB, 512 blocks of 2x4, 512->512, 153 active
+            // 21.0 -> 15.7, but on 1024 such blocks with 26 to 36 % active 29.6 -> 31.7).
+            // Not with 4 chunks on more tiles, where one 150 KB workgroup per CU overlaps no
+            // tile's start and end (128->256 on 512 tiles, no index, 13.4 -> 14.8; 128->512 on
+            // 1024 tiles 12.9 -> 14.3 / 22.3 -> 27.5), nor with 8 chunks on at most 64 tiles
+            // (256->64 9.2 -> 10.0). The ranges between would be faster too (4 chunks on up
+            // to 256 tiles 8.8 -> 8.0, 8 chunks on 65 to 256 tiles 11.1 -> 10.4 / 21.1 -> 19.2
+            // and on 1024 21.2 -> 18.6 / 39.4 -> 37.7); they are in the pipelined form still,
+            // with the order of sums that they have had there.
             // More than 256 tiles keep K whole: two slices as workgroups of their own cost
             // 512->512 at stride 16 25 -> 32 us. A call without an index runs every tile: if
             // its slices are more workgroups than CUs, each tile's workgroup runs them in
@@ -1576,8 +1581,8 @@ bool choose_plan(const LayerGeom &g, Plan &best, bool dma = true)
                             a.nslot = a.HR * a.HC;
                             break;
                         }
-                // ws_bytes stays: which layers need the workspace, and are refused without it,
-                // is documented by shape and does not change with the form
+                // ws_bytes stays, also where K is whole and nothing is stored: which layers ask
+                // for the workspace, and are refused without it, is documented by shape
                 if (tiles > 256) {
                     a.ksplit = 1;
                     a.cps = nchunk;
@@ -1770,7 +1775,7 @@ hipError_t launch_one(const Plan &p, hipStream_t s)
                 if (p.wavek == 12) return launch_kernel(k_conv_wavek3<BF16, 12>, p, s);
             }
             // all-tap stages exist for the 64x64 tiles the planner gives them to
-                if constexpr (BM == 64 && BN == 64 && KS == 3)
+            if constexpr (BM == 64 && BN == 64 && KS == 3)
                 if (p.sg == 9) return launch_kernel(k_conv_pipe<BF16, BM, BN, KS, S, 9>, p, s);
             if constexpr (BM == 64 && BN == 64 && KS == 1) {
                 if (p.sg == 2 && p.wgs == 2) return launch_kernel(k_conv_pipe<BF16, BM, BN, KS, S, 2, 2>, p, s);
