@@ -267,9 +267,16 @@ hipError_t launch_conv_nchw_f32(const float *x, const float *w, const float *bia
     // blocks below 16 pixels are many (64x64 blocks of 2x2, 64 -> 64: 311 us with all
     // channels, 440 with 16), and at most 16 where blocks are few
     int most = fit;
-    if (npx >= 16 || g.total_blocks < 2048) most = std::max(4, 20 * kThreads / (g.cin * taps * kCo));
+    if (npx >= 16 || g.total_blocks < 2048)
+        most = std::max(4, (int)(20 * kThreads / ((long long)g.cin * taps * kCo)));
     if (g.total_blocks < 512) most = 4;
-    a.ct = kCo * std::min({groups, fit, most});
+    // ... and as many as it takes to stay below the 2^32 threads of a launch, past which the
+    // runtime launches nothing and reports no error. All groups do, for the 4e9 output
+    // elements and 2^20 blocks that a call can have.
+    auto workgroups = [&](int n) { return (size_t)g.total_blocks * a.parts * ((groups + n - 1) / n); };
+    most = std::min({groups, fit, most});
+    if (workgroups(most) >= (size_t)1 << 24) most = std::min(groups, fit);
+    a.ct = kCo * most;
     // an odd number of 16-byte units per row of weights: consecutive rows, which consecutive
     // threads write, start in other banks; not if that costs another chunk
     auto chunk = [&](int wp) {
@@ -287,9 +294,7 @@ hipError_t launch_conv_nchw_f32(const float *x, const float *w, const float *bia
     a.f_npx = make_div(a.npx);
     a.f_row = make_div(a.ci_t * taps);
     const size_t lds = (size_t)a.ci_t * per_ci;
-    // at most 2^20 * 15 workgroups, and twice the output elements in threads (parts and
-    // channel groups at least half full): below the runtime's 2^32 threads
-    const unsigned grid = (unsigned)g.total_blocks * a.parts * a.n_co_tiles;
+    const unsigned grid = (unsigned)workgroups(most);
     if (g.kh != g.kw) return launch_ks<0>(a, grid, lds, s);
     switch (g.kh) {
     case 1: return launch_ks<1>(a, grid, lds, s);

@@ -77,6 +77,17 @@ def test_conv_f32_integer_exact(B, case):
     assert np.array_equal(from_dev(dense, nhwc=False), want)
 
 
+def test_conv_f32_many_channels_on_many_blocks(B):
+    """1200 blocks of one pixel with 240000 output channels: 16 channels per workgroup would
+    be 2^32 threads and more."""
+    cout = 240000
+    x = (torch.arange(1200, device="cuda") % 7 - 3).float().reshape(1, 1, 30, 40)
+    w = (torch.arange(cout, device="cuda") % 5 - 2).float().reshape(cout, 1, 1, 1)
+    out = torch.full((1, cout, 30, 40), float("nan"), device="cuda")
+    B.bc_sparse_conv2d((1, 1, 1, 0, 0), x, B.BC_NCHW, w, None, None, out, (30, 40), None, None)
+    assert torch.equal(out, x * w.reshape(1, cout, 1, 1))
+
+
 def test_conv_f32_most_blocks(B):
     """2^20 blocks of one pixel with more output channels than 16 workgroups of 256 threads
     per block could cover within the runtime's 2^32 threads per launch."""
