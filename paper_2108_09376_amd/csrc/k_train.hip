@@ -836,12 +836,13 @@ hipError_t launch_conv_weight_grad(const uint16_t *x, const uint16_t *g, float *
                                    const LayerGeom &fwd, bool bf16, hipStream_t s)
 {
     // One kernel row per workgroup where the output divides into 8 x 8 tiles (us per launch,
-    // before -> with it: 3x3 64 -> 64 at 128 x 256 23.2 -> 16.6, 128 -> 128 at 64 x 128 19.6
-    // -> 16.0, 32 -> 64 stride 2 20.7 -> 15.6; 1x1 64 -> 128 13.9 -> 7.0), not for 3x3 layers
-    // below 1024 output pixels (8 x 16 pixels 4.8 -> 6.1), nor where the uniform offsets of
-    // a 64-row tile could pass 2 GiB, nor for maps not aligned to 16 bytes, which the
-    // requests to LDS need.
-    if ((((uintptr_t)x | (uintptr_t)g) & 15) == 0 && fwd.hout % 8 == 0 && fwd.wout % 8 == 0 && fwd.cin <= (1 << 18) &&
+    // before -> with it: 3x3 64 -> 64 at 128 x 256 24.1 -> 17.3, 128 -> 128 at 64 x 128 20.2
+    // -> 15.9, 32 -> 64 stride 2 21.2 -> 16.3; 1x1 64 -> 64 at 64 x 128 14.3 -> 6.5), not for
+    // 3x3 layers below 1024 output pixels (8 x 16 pixels 4.8 -> 6.1), nor where the uniform
+    // offsets of a 64-row tile could pass 2 GiB, nor for maps not aligned to 16 bytes, which
+    // the requests to LDS need.
+    const bool aligned = (((uintptr_t)x | (uintptr_t)g) & 15) == 0;
+    if (aligned && fwd.hout % 8 == 0 && fwd.wout % 8 == 0 && fwd.cin <= (1 << 18) &&
         (fwd.kh == 1 || fwd.n * fwd.hout * fwd.wout >= 1024)) {
         WgradRow R;
         R.hin = fwd.hin; R.win = fwd.win; R.cin = fwd.cin;
@@ -857,7 +858,7 @@ hipError_t launch_conv_weight_grad(const uint16_t *x, const uint16_t *g, float *
         // least near sqrt(6 KB * tiles / base), and up to 48 workgroups cost nothing. Not more
         // workgroups, db's among them, than run at once (a second round: 3x3 256 -> 256 at
         // 128 x 256, 79 us with 5 splits, 118 with 6; CUs with two of them and CUs with one,
-        // which 1x1 layers' LDS allows: 256 -> 256 at 256 x 256, 44 us with 400, 29 with 512),
+        // which 1x1 layers' LDS allows: 256 -> 256 at 256 x 256, 44 us with 400, 33 with 240),
         // nor more additions per address than 16 + one per 2048 pixels: each rounds the whole
         // sum (1x1 64 -> 64 at 64 x 128, values of one sign: error 7.2e-8 with the general
         // form, 6.4e-8 with 20 additions, 8.1e-8 with 32, 1.5e-7 with 128).
