@@ -132,15 +132,16 @@ hipError_t launch_conv_input_grad(const uint16_t *grad_out, const uint16_t *w, c
 hipError_t launch_conv_weight_grad(const uint16_t *x, const uint16_t *g, float *dw, float *db,
                                    const LayerGeom &fwd, bool bf16, hipStream_t s);
 // Multi-tensor RMSprop: up to kMaxParams tensors; first[t] is the first workgroup of
-// tensor t (first[n] = the grid), each workgroup covering kRmspropElems elements.
+// tensor t (first[n] = the grid), each workgroup covering kRmspropThreads * per elements.
 constexpr int kMaxParams = 64;
-constexpr int kRmspropElems = 1024;
+constexpr int kRmspropThreads = 256;
 struct RmspropMany {
     float *w[kMaxParams], *v[kMaxParams], *grad[kMaxParams];
     uint16_t *w16[kMaxParams];
     long long count[kMaxParams];
     int first[kMaxParams + 1];
     int n;
+    int per;                                   // elements per thread, 1 or 4
 };
 hipError_t launch_rmsprop_many(const RmspropMany &m, float lr, float alpha, float eps, float wd,
                                bool bf16, hipStream_t s);

@@ -687,17 +687,17 @@ __global__ __launch_bounds__(kThreads) void k_rmsprop(float *__restrict__ w, flo
 
 // Several tensors in one launch: workgroup b belongs to the tensor t with
 // first[t] <= b < first[t + 1] (a uniform scan over at most kMaxParams entries of the
-// kernel arguments), elements [(b - first[t]) * kRmspropElems, ...) of that tensor, four per
-// thread and all requested before the first is used (1.4 M parameters: 12.8 -> 8.2 us).
-template <bool BF16>
+// kernel arguments), elements [(b - first[t]) * kThreads * U, ...) of that tensor, U per
+// thread and all requested before the first is used (1.4 M parameters in 22 tensors: 12.8
+// us with U = 1, 8.2 with U = 4).
+template <bool BF16, int U>
 __global__ __launch_bounds__(kThreads) void k_rmsprop_many(RmspropMany m, float lr, float alpha,
                                                            float eps, float wd)
 {
-    constexpr int U = kRmspropElems / kThreads;
     const int b = blockIdx.x;
     int t = 0;
     while (t + 1 < m.n && m.first[t + 1] <= b) ++t;
-    const long long i0 = (long long)(b - m.first[t]) * kRmspropElems + threadIdx.x;
+    const long long i0 = (long long)(b - m.first[t]) * (kThreads * U) + threadIdx.x;
     float *w = m.w[t], *v = m.v[t], *grad = m.grad[t];
     const long long count = m.count[t];
     if (i0 >= count) return;
@@ -907,11 +907,11 @@ hipError_t launch_conv_weight_grad(const uint16_t *x, const uint16_t *g, float *
 hipError_t launch_rmsprop_many(const RmspropMany &m, float lr, float alpha, float eps, float wd,
                                bool bf16, hipStream_t s)
 {
+    static_assert(kThreads == kRmspropThreads, "workgroups counted by the caller");
     const dim3 grid((unsigned)m.first[m.n]), block(kThreads);
-    if (bf16)
-        hipLaunchKernelGGL(k_rmsprop_many<true>, grid, block, 0, s, m, lr, alpha, eps, wd);
-    else
-        hipLaunchKernelGGL(k_rmsprop_many<false>, grid, block, 0, s, m, lr, alpha, eps, wd);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, s, m, lr, alpha, eps, wd); };
+    if (m.per == 4) bf16 ? go(k_rmsprop_many<true, 4>) : go(k_rmsprop_many<false, 4>);
+    else bf16 ? go(k_rmsprop_many<true, 1>) : go(k_rmsprop_many<false, 1>);
     return hipGetLastError();
 }
 

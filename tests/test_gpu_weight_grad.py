@@ -110,10 +110,12 @@ def test_weight_grad_no_less_accurate_than_the_general_form(cin, cout, k):
     assert err[128][1] <= 1.3 * err[124][1]
 
 
-@pytest.mark.parametrize("counts", [(1, 255, 1024, 1025), (4096, 2049, 3)])
+@pytest.mark.parametrize("counts", [(1, 255, 1024, 1025), (4096, 2049, 3), (262145,), (300000, 5),
+                                    (1, 262144, 1023, 1024, 1025, 2049, 255, 256, 257)])
 def test_rmsprop_many_elements_per_workgroup(counts):
-    """Tensors that end inside, at and just past a workgroup's 1024 elements take the same
-    step as one by one, byte for byte, with and without a 16-bit copy."""
+    """Tensors that end inside, at and just past a workgroup's 256 or 1024 elements (few or
+    many workgroups) take the same step as one by one, byte for byte, with and without a
+    16-bit copy."""
     from paper_2108_09376_amd import bc
     r = synth.rng(7700 + len(counts))
     make = lambda: [tuple(torch.from_numpy(a).cuda() for a in t) for t in data]
