@@ -93,11 +93,11 @@ struct MfmaArgs {
     int ksplit, cps;                    // K slices per tile, 32-channel chunks per slice
     int kseq;                           // wave-K form: slices one workgroup runs in order
     int perm8;                          // wave-K form: rows permuted for 8-pixel-wide tiles
-    int tw, tpr;                        // wave-K form: tile width, tiles per row of the block
     int tiles_full;                     // tiles (incl. K slices) of a full frame
     int slots;                          // stem form: workgroups resident on the device
     int xu, gx;                         // XCD grouping of the tile order (xcd_tile), 0 = off
     int grp_lds;                        // pipelined form: LDS bytes of one wave group
+    int tw, tpr;                        // wave-K form: tile width, tiles per row of the block
 };
 
 template <bool BF16>
@@ -169,12 +169,11 @@ __device__ __forceinline__ bool load_tile_blocks(const MfmaArgs &a, int mt, Tile
             k = mt / a.tpb;
             const int t = mt - k * a.tpb;
             r0 = t * a.R;
-            if constexpr (CUT)
-                if (a.tpr > 1) {
-                    const int row = t / a.tpr;
-                    r0 = row * a.R;
-                    q0 = (t - row * a.tpr) * a.tw;
-                }
+            if constexpr (CUT) {
+                const int row = t / a.tpr;
+                r0 = row * a.R;
+                q0 = (t - row * a.tpr) * a.tw;
+            }
         } else {
             k = mt * a.P + tid;
             r0 = 0;
@@ -206,11 +205,11 @@ __device__ __forceinline__ bool load_tile_blocks(const MfmaArgs &a, int mt, Tile
 // the storage format and writes with 16-byte buffer stores; rows of inactive patches
 // use an out-of-range offset, which the hardware drops. `tid` is the thread's index in
 // its group of four waves; a group that is not `live` only takes the barriers.
-// PERM: a tile of one block is a.tw pixels wide, and its 64 rows may be permuted if that is
-// eight (a.perm8): row 16 mi + 8 h + c of the tile is pixel row mi + 4 h, column c.
+// PERM: the rows of a 64-row tile that is 8 pixels wide may be permuted (a.perm8): row
+// 16 mi + 8 h + c of the tile is pixel row mi + 4 h, column c. CUT: tiles are a.tw wide.
 __device__ __forceinline__ int perm8_row(int m) { return (((m >> 4) + 4 * ((m >> 3) & 1)) << 3) + (m & 7); }
 
-template <bool BF16, int BM, int BN, bool PERM = false>
+template <bool BF16, int BM, int BN, bool PERM = false, bool CUT = false>
 struct Epilogue {
     static constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 16;
     static constexpr int NP = WN / 32, NU = WM / 16;
@@ -232,7 +231,7 @@ struct Epilogue {
             bias[np][0] = bload(br, co * 4);
             bias[np][1] = bload(br, co * 4 + 16);
         }
-        const int bw = PERM ? a.tw : a.bw, rbw = a.R * bw;
+        const int bw = CUT ? a.tw : a.bw, rbw = a.R * bw;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             int m = wm * WM + (lane >> 2) + 16 * u;
@@ -942,7 +941,7 @@ __device__ __forceinline__ void join_waves(f32x4 (&acc)[4][4], f32x4 (&out)[2][2
 constexpr int wavek3_bytes(int HA, int D) { return 2 * HA * 1024 + D * 4096; }
 constexpr int wavek3_depth(int HA) { return HA <= 7 ? 6 : HA <= 9 ? 5 : 3; }
 
-template <bool BF16, int HA>
+template <bool BF16, int HA, bool CUT = false>
 __global__ __launch_bounds__(kThreads, 1) void k_conv_wavek3(MfmaArgs a)
 {
     constexpr int KT = 9, HB = HA * 1024, D = wavek3_depth(HA);
@@ -954,8 +953,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv_wavek3(MfmaArgs a)
     const int ks = L % a.ksplit, mn = L / a.ksplit;
     const int nt = mn % a.ntn, mt = mn / a.ntn;
     const int n0 = nt * 64;
-    if (!load_tile_blocks<true>(a, mt, tb)) return;   // tile beyond the active count (uniform)
-    Epilogue<BF16, 64, 64, true> epi;
+    if (!load_tile_blocks<CUT>(a, mt, tb)) return;   // tile beyond the active count (uniform)
+    Epilogue<BF16, 64, 64, true, CUT> epi;
     epi.prefetch(a, tb, n0);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -995,14 +994,14 @@ __global__ __launch_bounds__(kThreads, 1) void k_conv_wavek3(MfmaArgs a)
         dma16(wd, lring + slot * 4096 + v * 1024, c * BK + q * 8 < a.cin ? off : kOutOfRange);
     };
     int sl[4];                                           // halo slot of this lane's rows at tap (0, 0)
-    const int rbw = a.R * a.tw;
+    const int bw = CUT ? a.tw : a.bw, rbw = a.R * bw;
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi) {
         const int r = mi * 16 + (lane & 15);
         const int m = a.perm8 ? perm8_row(r) : r;
         const int p = fdiv(m, a.f_rbw);
         const int local = m - p * rbw;
-        const int pr = fdiv(local, a.f_bw), pc = local - pr * a.tw;
+        const int pr = fdiv(local, a.f_bw), pc = local - pr * bw;
         sl[mi] = p * hrhc + pr * a.HC + pc;
     }
     const int bo = (lane & 15) * 64 + (((lane >> 4) ^ ((lane >> 1) & 3)) << 4);
@@ -1770,6 +1769,7 @@ hipError_t launch_one(const Plan &p, hipStream_t s)
     } else if (p.form == Form::Pipe) {
         if constexpr (KS == 1 || KS == 3) {
             if constexpr (BM == 64 && BN == 64 && KS == 3 && S == 1) {
+                if (p.a.tpr > 1) return launch_kernel(k_conv_wavek3<BF16, 7, true>, p, s);   // 100 or 108 slots
                 if (p.wavek == 7) return launch_kernel(k_conv_wavek3<BF16, 7>, p, s);
                 if (p.wavek == 9) return launch_kernel(k_conv_wavek3<BF16, 9>, p, s);
                 if (p.wavek == 12) return launch_kernel(k_conv_wavek3<BF16, 12>, p, s);
