@@ -1567,7 +1567,7 @@ bool choose_plan(const LayerGeom &g, Plan &best, bool dma = true)
                 ((nchunk >= 8 && tiles > 256 && tiles <= 512) || (nchunk >= 16 && tiles <= 2048))) {
                 // The bands of 32-wide blocks are cut into 8x8 or 4x16 pixels, their halo being
                 // above 7 KB: requests fill LDS no faster than the products use it (256 -> 128, 4x32
-                // blocks, no index: 20.0 us in the pipelined form, 21.3 with 2x32 bands, 19.2
+                // blocks, no index: 20.0 us in the pipelined form, 21.2 with 2x32 bands, 18.6
                 // cut).
                 if (a.P == 1 && a.nslot > 112)
                     for (int e = 8; e <= 16; e *= 2)
