@@ -961,7 +961,8 @@ def swiftnet_clip_step(torch, bc, dev, frames=30, seed=2021):
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "sparse_conv_traffic_resnet50_2048x1024_active0.3.txt")
 MFMA_PROFILE = os.path.join(ROOT, "profiles", "sparse_conv_mfma_lds_resnet50_2048x1024_active0.3.txt")
-CONV_SOURCES = ("paper_2108_09376_amd/csrc/k_conv_mfma.hip", "paper_2108_09376_amd/csrc/bc_internal.h")
+CONV_SOURCES = ("paper_2108_09376_amd/csrc/k_conv_mfma.hip", "paper_2108_09376_amd/csrc/lds_dma.h",
+                "paper_2108_09376_amd/csrc/bc_internal.h")
 
 
 def code_sha(files):
